@@ -268,9 +268,9 @@ template <typename T> const cpx<T>* twiddles(const amap_ctx* c);
 template <> const cpx<float>* twiddles<float>(const amap_ctx* c) { return c->tw32; }
 template <> const cpx<double>* twiddles<double>(const amap_ctx* c) { return c->tw64; }
 
-// ---- direct-sum tap table ----------------------------------------------------------------
-static amap_status build_tap_table(amap_filter f, double theta, double fparam, double cut_px,
-                                   int n, TapTable* t) {
+// The cut radius of the direct sum: as given, or (cut_px <= 0) the filter's
+// natural support.
+static amap_status direct_cut(amap_filter f, double theta, double cut_px, int n, double* out) {
     double cut = cut_px;
     if (!(cut > 0.0)) {
         cut = f == AMAP_FILTER_STARLET ? 2.0 * theta : (f == AMAP_FILTER_S98 ? theta : 5.0 * theta);
@@ -281,29 +281,7 @@ static amap_status build_tap_table(amap_filter f, double theta, double fparam, d
     if (2 * R + 1 > n)
         return fail(AMAP_E_INVAL, "cut radius %g too large for n = %d (need 2*floor(cut)+1 <= n)",
                     cut, n);
-    const double c2 = cut * cut;
-    const int D = 2 * R + 1;
-    t->R = R;
-    t->half.assign(D, -1);
-    t->wc.assign((size_t)D * D, 0.0);
-    t->ws.assign((size_t)D * D, 0.0);
-    for (int dy = -R; dy <= R; ++dy) {
-        for (int dx = -R; dx <= R; ++dx) {
-            const double r2 = (double)(dx * dx + dy * dy);
-            if (r2 > c2) continue;
-            const int ax = dx < 0 ? -dx : dx;
-            if (ax > t->half[dy + R]) t->half[dy + R] = ax;
-            if (r2 == 0.0) continue;
-            const double r = std::sqrt(r2);
-            double q;
-            if (f == AMAP_FILTER_STARLET) q = starlet_Q(r / theta) / (theta * theta);
-            else if (f == AMAP_FILTER_S98) q = s98_Q(r, theta, fparam);
-            else q = jbj04_Q(r, theta, fparam);
-            const size_t i = (size_t)(dy + R) * D + (dx + R);
-            t->wc[i] = q * (double)(dx * dx - dy * dy) / r2;
-            t->ws[i] = q * 2.0 * (double)dx * (double)dy / r2;
-        }
-    }
+    *out = cut;
     return AMAP_OK;
 }
 
@@ -1046,53 +1024,6 @@ amap_status amap_starlet_reconstruct(amap_ctx_t c, amap_dtype dt, int n, int J,
 
 }  // extern "C"
 
-// Uploads the direct sum's tap tables into the context's workspace and
-// launches it: the row offsets' dx ranges, the dense weights and, for the
-// LDS row kernel, the weights regrouped by four dx (zero outside the disc).
-template <typename T>
-static amap_status enqueue_direct(amap_ctx* c, const TapTable& tab, int logn, const T* g1,
-                                  const T* g2, T* out, hipStream_t s) {
-    const int R = tab.R, D = 2 * R + 1;
-    const int R4 = (R + 3) / 4 * 4, ng = R4 / 2 + 1;
-    const bool grouped = map_direct_uses_groups(logn, R, sizeof(T));
-    const size_t off_w = align256((size_t)D * sizeof(int));
-    const size_t wbytes = align256((size_t)D * D * sizeof(T));
-    const size_t gbytes = grouped ? align256((size_t)D * ng * 8 * sizeof(T)) : 0;
-    AMAP_TRY(c->ws.reserve(off_w + 2 * wbytes + gbytes));
-    char* base = static_cast<char*>(c->ws.ptr);
-    std::vector<T> wc(tab.wc.begin(), tab.wc.end()), ws(tab.ws.begin(), tab.ws.end());
-    std::vector<T> gt;
-    if (grouped) {
-        gt.assign((size_t)D * ng * 8, (T)0);
-        for (int dy = -R; dy <= R; ++dy)
-            for (int k = 0; k < ng; ++k)
-                for (int q = 0; q < 4; ++q) {
-                    const int dx = 4 * k - R4 + q;
-                    if (dx < -R || dx > R) continue;
-                    const size_t src = (size_t)(dy + R) * D + (dx + R);
-                    const size_t dst = ((size_t)(dy + R) * ng + k) * 8;
-                    gt[dst + q] = (T)tab.wc[src];
-                    gt[dst + 4 + q] = (T)tab.ws[src];
-                }
-    }
-    // The tables are staged synchronously: the workspace may still be read by
-    // earlier work on this stream, so wait for it first.
-    AMAP_HIP(hipStreamSynchronize(s), "stream synchronize before table upload");
-    char* pc = base + off_w;
-    char* ps = pc + wbytes;
-    char* pg = ps + wbytes;
-    AMAP_HIP(hipMemcpy(base, tab.half.data(), (size_t)D * sizeof(int), hipMemcpyHostToDevice),
-             "upload tap rows");
-    AMAP_HIP(hipMemcpy(pc, wc.data(), wc.size() * sizeof(T), hipMemcpyHostToDevice), "upload taps");
-    AMAP_HIP(hipMemcpy(ps, ws.data(), ws.size() * sizeof(T), hipMemcpyHostToDevice), "upload taps");
-    if (grouped)
-        AMAP_HIP(hipMemcpy(pg, gt.data(), gt.size() * sizeof(T), hipMemcpyHostToDevice), "upload tap groups");
-    AMAP_HIP(launch_map_direct<T>(logn, g1, g2, R, (const int*)base, (const T*)pc, (const T*)ps,
-                                  grouped ? (const T*)pg : nullptr, out, s),
-             "direct aperture-mass kernel");
-    return AMAP_OK;
-}
-
 extern "C" {
 
 amap_status amap_map_direct(amap_ctx_t c, amap_dtype dt, int n, const void* g1, const void* g2,
@@ -1116,17 +1047,21 @@ amap_status amap_map_direct(amap_ctx_t c, amap_dtype dt, int n, const void* g1, 
     const size_t bytes = (size_t)n * n * esize(dt);
     if (overlaps(map_out, bytes, g1, bytes) || overlaps(map_out, bytes, g2, bytes))
         return fail(AMAP_E_INVAL, "map_out may not overlap the inputs");
-    TapTable tab;
-    AMAP_TRY(build_tap_table(filter, theta_px, fparam, cut_px, n, &tab));
+    double cut = 0.0;
+    AMAP_TRY(direct_cut(filter, theta_px, cut_px, n, &cut));
     DeviceGuard g(c->device);
     if (!g.ok) return fail(AMAP_E_HIP, "cannot select device %d", c->device);
     TimerScope ts(c);
+    AMAP_TRY(c->ws.reserve(direct_workspace_bytes((int)cut, esize(dt))));
     const int logn = ilog2(n);
-    return dt == AMAP_F32
-        ? enqueue_direct<float>(c, tab, logn, (const float*)g1, (const float*)g2, (float*)map_out,
-                                static_cast<hipStream_t>(stream))
-        : enqueue_direct<double>(c, tab, logn, (const double*)g1, (const double*)g2, (double*)map_out,
-                                 static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    AMAP_HIP(dt == AMAP_F32
+                 ? launch_map_direct<float>(logn, (const float*)g1, (const float*)g2, (int)filter, theta_px,
+                                            fparam, cut, c->ws.ptr, (float*)map_out, s)
+                 : launch_map_direct<double>(logn, (const double*)g1, (const double*)g2, (int)filter, theta_px,
+                                             fparam, cut, c->ws.ptr, (double*)map_out, s),
+             "direct aperture-mass kernels");
+    return AMAP_OK;
 }
 
 static amap_status validate_noise(amap_dtype dt, int n, int J, const void* g1, const void* g2,
