@@ -141,7 +141,7 @@ template <typename T> bool plan_valid(int n, int J, bool noise, const StagePlan&
 template <typename T>
 hipError_t launch_peak_hist(int logn, int nplanes, const T* planes, int sign, double lo,
                             double width, int nbins, long long* hist, hipStream_t s);
-// Blocks per plane of the moment reductions (their partials: 3 x nplanes x this doubles).
+// Blocks per plane of the moment reductions (their partials: 4 x nplanes x this doubles).
 int moment_blocks(int logn);
 template <typename T>
 hipError_t launch_plane_moments(int logn, int nplanes, const T* planes, double* part, double* out4,

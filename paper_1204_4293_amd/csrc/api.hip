@@ -1171,7 +1171,7 @@ amap_status amap_plane_moments(amap_ctx_t c, amap_dtype dt, int n, int nplanes, 
     if (!g.ok) return fail(AMAP_E_HIP, "cannot select device %d", c->device);
     TimerScope ts(c);
     const int logn = ilog2(n);
-    AMAP_TRY(c->ws.reserve((size_t)3 * nplanes * moment_blocks(logn) * sizeof(double)));
+    AMAP_TRY(c->ws.reserve((size_t)4 * nplanes * moment_blocks(logn) * sizeof(double)));
     hipStream_t s = static_cast<hipStream_t>(stream);
     double* part = static_cast<double*>(c->ws.ptr);
     hipError_t e = dt == AMAP_F32

@@ -109,44 +109,71 @@ k_count_peaks(const T* __restrict__ snr, int logn, double thr, long long* __rest
 // Histogram of peak heights (Sec. 2.2): pixels that are strict 8-neighbour
 // maxima of sign*value, periodic, binned by h = sign*value into nbins equal
 // bins over [lo, lo + nbins*width); the bin is floor((h - lo) / width) in
-// double.  grid (blocks, nplanes) of 1024 threads, each block striding over
-// its plane a pixel per thread at a time (at most 64 blocks per plane);
-// counts gather in LDS and are added to hist once per block and bin.
+// double.  A thread takes four columns of kHistRows rows: it loads their
+// window (a 4-vector and two edge values per row) before any test, keeps one
+// bit per peak, then bins its peaks one at a time, so a wavefront divides as
+// often as its busiest lane has peaks (reading heights again from L1) and
+// not once per pixel.  Counts gather in LDS and are added to hist once per
+// block and bin; grid (blocks, nplanes), blocks striding over the plane.
+// Bound by the loads: six 1024^2 float planes, 40 bins in 11 us (24.5 us with
+// nine loads per pixel, one pixel at a time).
+constexpr int kHistRows = 8, kHistNT = 256;
 template <typename T>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(kHistNT)
 k_peak_hist(const T* __restrict__ planes, int logn, int sign, double lo, double width, int nbins,
             long long* __restrict__ hist) {
     extern __shared__ unsigned int bins[];
-    for (int b = threadIdx.x; b < nbins; b += 1024) bins[b] = 0u;
+    for (int b = threadIdx.x; b < nbins; b += kHistNT) bins[b] = 0u;
     __syncthreads();
+    constexpr int K = kHistRows;
+    static_assert(4 * K == 32, "one bit per pixel of a thread");
     const int n = 1 << logn, m = n - 1;
     const long long n2 = (long long)n * n;
     const T* p = planes + (long long)blockIdx.y * n2;
-    for (long long idx = (long long)blockIdx.x * 1024 + threadIdx.x; idx < n2;
-         idx += (long long)gridDim.x * 1024) {
-        const int x = (int)(idx & m), y = (int)(idx >> logn);
-        const T h = sign > 0 ? p[idx] : -p[idx];
-        // the eight neighbour loads issue together, then one test
-        T q[8];
-        int k = 0;
+    const int lc = logn - 2;                          // log2 vector columns
+    const int items = (n / K) << lc;                  // (strip of K rows, vector column)
+    for (int it = blockIdx.x * kHistNT + threadIdx.x; it < items; it += gridDim.x * kHistNT) {
+        const int x = (it & ((1 << lc) - 1)) * 4, y0 = (it >> lc) * K;
+        T r[K + 2][6];  // rows y0 - 1 .. y0 + K at columns x - 1 .. x + 4
 #pragma unroll
-        for (int dy = -1; dy <= 1; ++dy) {
-            const long long row = (long long)((y + dy) & m) * n;
+        for (int a = 0; a < K + 2; ++a) {
+            const T* row = p + (long long)((y0 + a - 1) & m) * n;
+            r[a][0] = row[(x - 1) & m];
 #pragma unroll
-            for (int dx = -1; dx <= 1; ++dx)
-                if (dy != 0 || dx != 0) q[k++] = p[row + ((x + dx) & m)];
+            for (int b = 0; b < 4; ++b) r[a][1 + b] = row[x + b];
+            r[a][5] = row[(x + 4) & m];
         }
-        bool peak = true;
+        if (sign < 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) peak = peak & (h > (sign > 0 ? q[i] : -q[i]));
-        if (peak) {
-            const double b = floor(((double)h - lo) / width);
+            for (int a = 0; a < K + 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 6; ++b) r[a][b] = -r[a][b];
+        }
+        unsigned int found = 0u;
+#pragma unroll
+        for (int a = 0; a < K; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const T v = r[a + 1][b + 1];
+                bool pk = true;
+#pragma unroll
+                for (int da = 0; da < 3; ++da)
+#pragma unroll
+                    for (int db = 0; db < 3; ++db)
+                        if (da != 1 || db != 1) pk = pk & (v > r[a + da][b + db]);
+                found |= (pk ? 1u : 0u) << (4 * a + b);
+            }
+        while (found) {
+            const int k = __builtin_ctz(found);
+            found &= found - 1u;
+            const T v = p[(long long)(y0 + (k >> 2)) * n + x + (k & 3)];
+            const double b = floor(((double)(sign > 0 ? v : -v) - lo) / width);
             if (b >= 0.0 && b < (double)nbins) atomicAdd(&bins[(int)b], 1u);
         }
     }
     __syncthreads();
     long long* out = hist + (long long)blockIdx.y * nbins;
-    for (int b = threadIdx.x; b < nbins; b += 1024)
+    for (int b = threadIdx.x; b < nbins; b += kHistNT)
         if (bins[b]) atomicAdd((unsigned long long*)&out[b], (unsigned long long)bins[b]);
 }
 
@@ -163,59 +190,91 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
     return t;
 }
 
-// Pass 1: per-block sums of a plane (grid (nb, nplanes)); pass 2 (mean
-// given): per-block sums of (x - mean)^k, k = 2, 3, 4.  part is
-// [3][nplanes][nb].
+// Sum of a plane's nb partials by a block of 256 threads (fixed order).
+__device__ __forceinline__ double fold256(const double* __restrict__ part, int nb, double* sh) {
+    double v = 0.0;
+    for (int b = threadIdx.x; b < nb; b += 256) v += part[b];
+    return block_sum256(v, sh);
+}
+
+// Pass 1: per-block sums of a plane (grid (nb, nplanes)) into part; pass 2
+// (CENTRAL): every block folds those nb sums to the plane's mean (they come
+// from L2; a launch of their own took 3 us), then its sums of (x - mean)^k, k = 2, 3, 4, into
+// cpart [3][nplanes][nb].  Both passes are bound by their reads of the planes.
 template <typename T, bool CENTRAL>
 __global__ void __launch_bounds__(256)
-k_moment_part(const T* __restrict__ planes, long long n2, const double* __restrict__ out4,
-              double* __restrict__ part) {
+k_moment_part(const T* __restrict__ planes, long long n2, double* __restrict__ part,
+              double* __restrict__ cpart) {
     __shared__ double sh[4];
+    constexpr int G = 16 / (int)sizeof(T);  // n2 is a multiple of 256
+    typedef T vec __attribute__((ext_vector_type(G)));
     const int pl = blockIdx.y, nb = gridDim.x;
-    const T* p = planes + (long long)pl * n2;
-    const double mu = CENTRAL ? out4[4 * pl] : 0.0;
+    const vec* p = reinterpret_cast<const vec*>(planes + (long long)pl * n2);
+    const long long nv = n2 / G;
+    double* mine = part + (long long)pl * nb;
+    const long long stride = (long long)nb * 256;
+    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    // the first vectors are on their way while the mean is folded
+    constexpr int U = 4;
+    vec v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i + u * stride < nv ? p[i + u * stride] : vec(0);
+    const double mu = CENTRAL ? fold256(mine, nb, sh) / (double)n2 : 0.0;
     double s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n2; i += (long long)nb * 256) {
-        const double d = (double)p[i] - mu;
-        if (CENTRAL) {
-            const double d2 = d * d;
-            s1 += d2;
-            s2 += d2 * d;
-            s3 += d2 * d2;
-        } else {
-            s1 += d;
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + u * stride >= nv) continue;
+#pragma unroll
+            for (int c = 0; c < G; ++c) {
+                const double d = (double)v[u][c] - mu;
+                if (CENTRAL) {
+                    const double d2 = d * d;
+                    s1 += d2;
+                    s2 += d2 * d;
+                    s3 += d2 * d2;
+                } else {
+                    s1 += d;
+                }
+            }
         }
+        i += U * stride;
+        if (i >= nv) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = i + u * stride < nv ? p[i + u * stride] : vec(0);
     }
-    const long long o = (long long)pl * nb + blockIdx.x;
-    const long long stride = (long long)gridDim.y * nb;
     const double t1 = block_sum256(s1, sh);
     if (!CENTRAL) {
-        if (threadIdx.x == 0) part[o] = t1;
+        if (threadIdx.x == 0) mine[blockIdx.x] = t1;
         return;
     }
     const double t2 = block_sum256(s2, sh);
     const double t3 = block_sum256(s3, sh);
     if (threadIdx.x == 0) {
-        part[o] = t1;
-        part[stride + o] = t2;
-        part[2 * stride + o] = t3;
+        const long long o = (long long)pl * nb + blockIdx.x;
+        const long long ps = (long long)gridDim.y * nb;
+        cpart[o] = t1;
+        cpart[ps + o] = t2;
+        cpart[2 * ps + o] = t3;
     }
 }
 
 // Folds the nb partials of each plane (one block per plane, fixed order):
-// the mean (pass 1) or m2, m3, m4 (pass 2) into out4[4 * plane + ...].
-template <bool CENTRAL>
+// the mean and m2, m3, m4 into out4[4 * plane ...].
 __global__ void __launch_bounds__(256)
-k_moment_fold(const double* __restrict__ part, int nb, long long n2, double* __restrict__ out4) {
+k_moment_fold(const double* __restrict__ part, const double* __restrict__ cpart, int nb, long long n2,
+              double* __restrict__ out4) {
     __shared__ double sh[4];
     const int pl = blockIdx.x, np = gridDim.x;
-    const long long stride = (long long)np * nb;
-    const int K = CENTRAL ? 3 : 1;
-    for (int k = 0; k < K; ++k) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nb; b += 256) v += part[k * stride + (long long)pl * nb + b];
-        const double t = block_sum256(v, sh);
-        if (threadIdx.x == 0) out4[4 * pl + (CENTRAL ? 1 + k : 0)] = t / (double)n2;
+    const long long stride = (long long)np * nb, o = (long long)pl * nb;
+    const double mu = fold256(part + o, nb, sh);
+    double mk[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) mk[k] = fold256(cpart + k * stride + o, nb, sh);
+    if (threadIdx.x == 0) {
+        out4[4 * pl] = mu / (double)n2;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) out4[4 * pl + 1 + k] = mk[k] / (double)n2;
     }
 }
 
@@ -232,10 +291,14 @@ k_phase_u32(int logn, uint64_t seed, uint64_t r, uint32_t* __restrict__ out) {
 }
 
 static unsigned blocks_for(long long count) { return (unsigned)((count + 255) / 256); }
-// Blocks per plane for the peak histogram: chunks of 1024 pixels, at most 64.
-static unsigned hist_blocks(long long n2) {
-    const long long chunks = (n2 + 1023) / 1024;
-    return (unsigned)(chunks < 64 ? chunks : 64);
+// Blocks per plane for the peak histogram: one per kHistNT items, at most 128
+// or, for few planes, enough for 1024 blocks in all (each block adds its
+// non-empty bins to the plane's, so there are few of them).
+static unsigned hist_blocks(long long n2, int nplanes) {
+    const long long items = n2 / (4 * kHistRows);
+    long long b = (items + kHistNT - 1) / kHistNT;
+    const long long most = 1024 / nplanes > 128 ? 1024 / nplanes : 128;
+    return (unsigned)(b > most ? most : b);
 }
 // Blocks per plane for the peak count: chunks of 4096 pixels, at most 64
 // blocks (so at most 64 atomic adds per plane's counter).
@@ -286,15 +349,15 @@ hipError_t launch_peak_hist(int logn, int nplanes, const T* planes, int sign, do
     hipError_t e = launch_zero_i64(hist, (long long)nplanes * nbins, s);
     if (e != hipSuccess) return e;
     AMAP_LAUNCH("peak_hist", s,
-                k_peak_hist<T><<<dim3(hist_blocks(n2), nplanes), 1024, nbins * sizeof(unsigned int), s>>>(
+                k_peak_hist<T><<<dim3(hist_blocks(n2, nplanes), nplanes), kHistNT, nbins * sizeof(unsigned int), s>>>(
                     planes, logn, sign, lo, width, nbins, hist));
     return hipGetLastError();
 }
 
 int moment_blocks(int logn) {
     const long long n2 = 1ll << (2 * logn);
-    long long nb = n2 / (256 * 8);  // about eight values per thread
-    return (int)(nb < 1 ? 1 : (nb > 1024 ? 1024 : nb));
+    const long long nb = n2 / (256 * 16);  // sixteen values per thread or more
+    return (int)(nb < 1 ? 1 : (nb > 256 ? 256 : nb));  // few enough blocks to run at once
 }
 
 template <typename T>
@@ -302,12 +365,12 @@ hipError_t launch_plane_moments(int logn, int nplanes, const T* planes, double* 
                                 hipStream_t s) {
     const long long n2 = 1ll << (2 * logn);
     const int nb = moment_blocks(logn);
+    double* cpart = part + (long long)nplanes * nb;
     AMAP_LAUNCH("moments_mean", s,
-                k_moment_part<T, false><<<dim3(nb, nplanes), 256, 0, s>>>(planes, n2, out4, part));
-    AMAP_LAUNCH("moments_fold", s, k_moment_fold<false><<<nplanes, 256, 0, s>>>(part, nb, n2, out4));
+                k_moment_part<T, false><<<dim3(nb, nplanes), 256, 0, s>>>(planes, n2, part, cpart));
     AMAP_LAUNCH("moments_central", s,
-                k_moment_part<T, true><<<dim3(nb, nplanes), 256, 0, s>>>(planes, n2, out4, part));
-    AMAP_LAUNCH("moments_fold", s, k_moment_fold<true><<<nplanes, 256, 0, s>>>(part, nb, n2, out4));
+                k_moment_part<T, true><<<dim3(nb, nplanes), 256, 0, s>>>(planes, n2, part, cpart));
+    AMAP_LAUNCH("moments_fold", s, k_moment_fold<<<nplanes, 256, 0, s>>>(part, cpart, nb, n2, out4));
     return hipGetLastError();
 }
 
