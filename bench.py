@@ -70,10 +70,9 @@ def kernel_model(name, n, J, batch_real, stage_starts=()):
     the part of that work it carries out: the column pass the forward
     column FFTs (and the phases), the row pass the forward and inverse row
     FFTs and the multiply, the inverse column pass the inverse column FFTs.
-    The paired kernels (ks_rows_pair, ks_cols_inv_pair) finish two
-    realisations' inverse transforms in one (their kappa_E are the real and
-    imaginary parts of one transform), so they complete the credited work
-    with half of the inverse arithmetic.
+    Two columns of kappa_E share one inverse transform (as its real and
+    imaginary parts), so the row and inverse column passes complete the
+    credited work with half of the inverse arithmetic.
 
     bytes: the kernel's design hand-offs, each operand read or written once
     per launch (the shared shear map once per launch; the double-precision
@@ -91,17 +90,16 @@ def kernel_model(name, n, J, batch_real, stage_starts=()):
     n2 = float(n * n)
     lg = n.bit_length() - 1
     B = batch_real
-    P = (B + 1) // 2  # realisation pairs
     fft1d = 5.0 * n2 * lg  # n transforms of length n
     models = {
         "ks_cols_fwd_rotate": (8.0 * n2 + 8.0 * n2 * B, B * (fft1d + 50.0 * n2)),
         "ks_cols_fwd": (16.0 * n2, fft1d),
-        "ks_rows": (16.0 * n2, 2 * fft1d + 6.0 * n2),
-        "ks_cols_inv": (12.0 * n2, fft1d),
-        # read B spectra, write P packed ones
-        "ks_rows_pair": (8.0 * n2 * (B + P), B * (2 * fft1d + 6.0 * n2)),
-        # read P packed spectra, write B real maps
-        "ks_cols_inv_pair": (8.0 * n2 * P + 4.0 * n2 * B, B * fft1d),
+        # read the spectrum, write the packed one (half of it)
+        "ks_rows": (12.0 * n2, 2 * fft1d + 6.0 * n2),
+        "ks_rows_noise": (12.0 * n2 * B, B * (2 * fft1d + 6.0 * n2)),
+        # read the packed spectrum, write the real map
+        "ks_cols_inv": (8.0 * n2, fft1d),
+        "ks_cols_inv_noise": (8.0 * n2 * B, B * fft1d),
         "noise_finalize": ((16.0 + 12.0) * (J - 1) * n2, 3.0 * (J - 1) * n2),
         "count_peaks": (4.0 * (J - 1) * n2, 9.0 * (J - 1) * n2),
     }
@@ -118,7 +116,7 @@ def kernel_model(name, n, J, batch_real, stage_starts=()):
     return models.get(name, (None, None))
 
 
-NOISE_KERNELS = ("ks_cols_fwd_rotate", "ks_rows_pair", "ks_cols_inv_pair", "merge_partials")
+NOISE_KERNELS = ("ks_cols_fwd_rotate", "ks_rows_noise", "ks_cols_inv_noise", "merge_partials")
 
 
 def compulsory_bytes(name, n, J):

@@ -221,7 +221,7 @@ amap_status amap_starlet_forward_bc(amap_ctx_t ctx, amap_dtype dt, int ny, int n
  * is written to kappa_e / kappa_b (ny*nx each, row-major).  P = n for an
  * n x n field is amap_ks_invert itself; P = 2 max(ny, nx) keeps the periodic
  * images of the field from overlapping it.  Outputs may not alias inputs.
- * Uses 6 P^2 elements of the context's workspace.
+ * Uses 2 P^2 elements of the context's workspace.
  */
 amap_status amap_ks_invert_padded(amap_ctx_t ctx, amap_dtype dt, int ny, int nx, int P,
                                   const void* g1, const void* g2, void* kappa_e,

@@ -10,6 +10,7 @@ namespace amap {
 
 constexpr int kMaxLogN = 12;          // largest map side 4096
 constexpr int kMaxN = 1 << kMaxLogN;
+constexpr int kTwiddles = 2 * kMaxN;  // tables of exp(-2 pi i k / N), N = 4096, 2048, ..., 1
 
 template <typename T>
 struct cpx {

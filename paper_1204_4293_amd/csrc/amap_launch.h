@@ -46,7 +46,7 @@ struct KsArgs {
     bool rotate;
     uint64_t seed;
     uint64_t r0;
-    const cpx<T>* tw;  // exp(-2 pi i k / 4096), k < 4096
+    const cpx<T>* tw;  // kTwiddles values: exp(-2 pi i k / N), k < N, for N = 4096, 2048, ...
     hipStream_t stream;
     // grouped maps: device tables of per-map element offsets from g1, g2, kE
     // (null: b * stride).  Offsets from a kernel-argument pointer keep the
@@ -54,10 +54,10 @@ struct KsArgs {
     const long long* g1_off = nullptr;
     const long long* g2_off = nullptr;
     const long long* kE_off = nullptr;
-    // kappa_B not wanted (kB ignored): where supported, maps 2p and 2p+1
-    // share one inverse transform (their Hermitian parts packed as
-    // H_2p + i H_2p+1); C is overwritten either way.  Needs kE_off == null.
-    bool pair_e = false;
+    // a field that is zero outside ny x nx pixels at the grid's origin (0: the
+    // whole grid): g1, g2, kE and kB are ny x nx, row-major, and realisations
+    // count their phases by the field's flat pixel index
+    int ny = 0, nx = 0;
 };
 template <typename T> hipError_t launch_ks(const KsArgs<T>& a);
 
@@ -186,29 +186,11 @@ template <typename T>
 hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T* planes, T* tmp,
                              int maps, long long image_stride, long long planes_stride, hipStream_t s);
 
-// Zero extension of an ny x nx pair of fields into P x P arrays, and the
-// ny x nx rectangles of `maps` P x P arrays (in_stride apart) read back
-// (out_stride apart; kB_p/kB may be null).
-template <typename T>
-hipError_t launch_pad2(const T* g1, const T* g2, int ny, int nx, int P, T* p1, T* p2, hipStream_t s);
-template <typename T>
-hipError_t launch_crop2(const T* kE_p, const T* kB_p, int P, int ny, int nx, T* kE, T* kB, int maps,
-                        long long in_stride, long long out_stride, hipStream_t s);
-
-// Noise realisations of a bounded field: the ny x nx shears rotated by the
-// Philox phases of realisations r0 .. r0+nb-1 (flat pixel index y*nx + x)
-// and written into the field's rectangle of each realisation's P x P
-// arrays (p_stride apart; their rest is left as it is: cleared once by
-// launch_zero2); Welford's update of the running mean M and squared
-// deviations M2 (double, `count` elements) with the values of realisations
-// r0 .. r0+nb-1 in order, w_stride apart (realisation 0 writes them unread);
+// Welford's update of the running mean M and squared deviations M2 (double,
+// `count` elements) with the values of realisations r0 .. r0+nb-1 in order,
+// w_stride apart (realisation 0 writes them unread);
 // sigma = sqrt(M2/(R-1)) and, if snr is not null, snr = w_signal / sigma (0
 // where sigma = 0).
-template <typename T>
-hipError_t launch_rotate_scatter(const T* g1, const T* g2, int ny, int nx, int P, uint64_t seed,
-                                 uint64_t r0, int nb, T* p1, T* p2, long long p_stride, hipStream_t s);
-template <typename T>
-hipError_t launch_zero2(T* p1, T* p2, long long count, hipStream_t s);
 template <typename T>
 hipError_t launch_welford_bc(const T* w, long long w_stride, int nb, double* M, double* M2,
                              long long count, int r0, hipStream_t s);

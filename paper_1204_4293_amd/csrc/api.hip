@@ -244,15 +244,18 @@ void Workspace::release() {
 }
 
 // ---- twiddles ----------------------------------------------------------------------
-// exp(-2 pi i k / 4096), evaluated in long double and rounded once.
+// exp(-2 pi i k / N) for N = 4096, 2048, ..., 1, one table after the other,
+// evaluated in long double and rounded once.
 template <typename T>
 static amap_status upload_twiddles(cpx<T>** out) {
-    std::vector<T> host(2 * kMaxN);
-    for (int k = 0; k < kMaxN; ++k) {
-        const long double a = -2.0L * 3.14159265358979323846264338327950288L * k / kMaxN;
-        host[2 * k] = (T)cosl(a);
-        host[2 * k + 1] = (T)sinl(a);
-    }
+    std::vector<T> host(2 * kTwiddles);
+    size_t at = 0;
+    for (int N = kMaxN; N >= 1; N /= 2)
+        for (int k = 0; k < N; ++k, ++at) {
+            const long double a = -2.0L * 3.14159265358979323846264338327950288L * k / N;
+            host[2 * at] = (T)cosl(a);
+            host[2 * at + 1] = (T)sinl(a);
+        }
     void* p = nullptr;
     if (hipMalloc(&p, host.size() * sizeof(T)) != hipSuccess)
         return fail(AMAP_E_NOMEM, "cannot allocate twiddle table");
@@ -291,12 +294,11 @@ namespace amap {
 template <typename T>
 amap_status enqueue_ks(const amap_ctx* ctx, int logn, int batch, const T* g1, const T* g2,
                        long long g_stride, cpx<T>* C, T* kE, T* kB, long long out_stride,
-                       bool rotate, uint64_t seed, uint64_t r0, hipStream_t s,
-                       bool pair_e = false) {
+                       bool rotate, uint64_t seed, uint64_t r0, hipStream_t s, int ny = 0, int nx = 0) {
     KsArgs<T> a;
     a.logn = logn; a.batch = batch; a.g1 = g1; a.g2 = g2; a.g_stride = g_stride; a.C = C;
     a.kE = kE; a.kB = kB; a.out_stride = out_stride; a.rotate = rotate; a.seed = seed;
-    a.r0 = r0; a.tw = twiddles<T>(ctx); a.stream = s; a.pair_e = pair_e;
+    a.r0 = r0; a.tw = twiddles<T>(ctx); a.stream = s; a.ny = ny; a.nx = nx;
     AMAP_HIP(launch_ks<T>(a), "KS kernels");
     return AMAP_OK;
 }
@@ -372,7 +374,7 @@ amap_status enqueue_noise(const amap_ctx* ctx, char* ws, int n, int J, const T* 
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int bb = (n_real - r0) < B ? (n_real - r0) : B;
         AMAP_TRY(enqueue_ks<T>(ctx, logn, bb, g1, g2, 0, C, kap, nullptr, n2, true, seed,
-                               (uint64_t)r0, s, /*pair_e=*/true));
+                               (uint64_t)r0, s));
         StarletArgs<T> a;
         a.logn = logn; a.J = J; a.batch = bb; a.done = r0; a.kappa = kap; a.in_stride = n2;
         a.planes = nullptr; a.planes_stride = 0; a.cbuf0 = cb0; a.cbuf1 = cb1; a.tmp = tmp;
@@ -794,31 +796,15 @@ amap_status amap_ks_invert_padded(amap_ctx_t c, amap_dtype dt, int ny, int nx, i
     DeviceGuard g(c->device);
     if (!g.ok) return fail(AMAP_E_HIP, "cannot select device %d", c->device);
     TimerScope ts(c);
-    // workspace: complex spectrum (2 planes), padded g1, g2, kappa_E, kappa_B
-    const size_t pb = align256((size_t)P * P * esize(dt));
-    AMAP_TRY(c->ws.reserve(6 * pb));
+    AMAP_TRY(c->ws.reserve(2 * align256((size_t)P * P * esize(dt))));  // the complex spectrum
     hipStream_t s = static_cast<hipStream_t>(stream);
-    char* w = static_cast<char*>(c->ws.ptr);
     const int logn = ilog2(P);
-    if (dt == AMAP_F32) {
-        float *p1 = (float*)(w + 2 * pb), *p2 = (float*)(w + 3 * pb);
-        float *e = (float*)(w + 4 * pb), *b = kappa_b ? (float*)(w + 5 * pb) : nullptr;
-        AMAP_HIP(launch_pad2<float>((const float*)g1, (const float*)g2, ny, nx, P, p1, p2, s), "pad kernel");
-        AMAP_TRY(enqueue_ks<float>(c, logn, 1, p1, p2, 0, (cpx<float>*)w, e, b, (long long)P * P,
-                                   false, 0, 0, s));
-        AMAP_HIP(launch_crop2<float>(e, b, P, ny, nx, (float*)kappa_e, (float*)kappa_b, 1, 0, 0, s),
-                 "crop kernel");
-    } else {
-        double *p1 = (double*)(w + 2 * pb), *p2 = (double*)(w + 3 * pb);
-        double *e = (double*)(w + 4 * pb), *b = kappa_b ? (double*)(w + 5 * pb) : nullptr;
-        AMAP_HIP(launch_pad2<double>((const double*)g1, (const double*)g2, ny, nx, P, p1, p2, s),
-                 "pad kernel");
-        AMAP_TRY(enqueue_ks<double>(c, logn, 1, p1, p2, 0, (cpx<double>*)w, e, b, (long long)P * P,
-                                    false, 0, 0, s));
-        AMAP_HIP(launch_crop2<double>(e, b, P, ny, nx, (double*)kappa_e, (double*)kappa_b, 1, 0, 0, s),
-                 "crop kernel");
-    }
-    return AMAP_OK;
+    const long long fn = (long long)ny * nx;
+    if (dt == AMAP_F32)
+        return enqueue_ks<float>(c, logn, 1, (const float*)g1, (const float*)g2, 0, (cpx<float>*)c->ws.ptr,
+                                 (float*)kappa_e, (float*)kappa_b, fn, false, 0, 0, s, ny, nx);
+    return enqueue_ks<double>(c, logn, 1, (const double*)g1, (const double*)g2, 0, (cpx<double>*)c->ws.ptr,
+                              (double*)kappa_e, (double*)kappa_b, fn, false, 0, 0, s, ny, nx);
 }
 
 static amap_status count_peaks_bc_impl(amap_ctx_t c, amap_dtype dt, int ny, int nx, int nplanes,
@@ -904,10 +890,10 @@ amap_status amap_mask_shear(amap_ctx_t c, amap_dtype dt, int ny, int nx, const u
 }  // extern "C"
 
 // Realisations per launch of the bounded noise path: as many as fit about
-// 1 GiB of workspace (P^2 spectrum, padded shears and kappa per
-// realisation, plus its field-sized kappa, scratch and planes), 1 .. 32.
+// 1 GiB of workspace (a P^2 spectrum, and a field-sized kappa, scratch and
+// planes per realisation), 1 .. 32.
 static int bounded_noise_batch(int ny, int nx, int P, int J, size_t esz, int n_real) {
-    const size_t per = 5 * (size_t)P * P * esz + (size_t)(2 + J) * ny * nx * esz;
+    const size_t per = 2 * (size_t)P * P * esz + (size_t)(2 + J) * ny * nx * esz;
     size_t b = ((size_t)1 << 30) / per;
     if (b < 1) b = 1;
     if (b > 32) b = 32;
@@ -916,7 +902,7 @@ static int bounded_noise_batch(int ny, int nx, int P, int J, size_t esz, int n_r
 }
 static size_t bounded_noise_bytes(int ny, int nx, int P, int J, size_t esz, int B) {
     const size_t pp = (size_t)P * P * esz * B, ff = (size_t)ny * nx * esz * B;
-    return align256(2 * pp) + 3 * align256(pp) + 2 * align256(ff) + align256(ff * J) +
+    return align256(2 * pp) + 2 * align256(ff) + align256(ff * J) +
            2 * align256((size_t)(J - 1) * ny * nx * 8);
 }
 
@@ -930,23 +916,15 @@ static amap_status enqueue_noise_bc(const amap_ctx* c, char* w, int ny, int nx, 
     const long long cnt = (long long)(J - 1) * fn;
     char* q = w;
     cpx<T>* C = reinterpret_cast<cpx<T>*>(q);  q += align256(2 * pp);
-    T* p1 = reinterpret_cast<T*>(q);           q += align256(pp);
-    T* p2 = reinterpret_cast<T*>(q);           q += align256(pp);
-    T* ke = reinterpret_cast<T*>(q);           q += align256(pp);
     T* kap = reinterpret_cast<T*>(q);          q += align256(ff);
     T* tmp = reinterpret_cast<T*>(q);          q += align256(ff);
     T* pl = reinterpret_cast<T*>(q);           q += align256(ff * J);
     double* M = reinterpret_cast<double*>(q);  q += align256((size_t)cnt * 8);
     double* M2 = reinterpret_cast<double*>(q);
-    // the grids outside the field stay zero: the KS never writes its inputs
-    AMAP_HIP(launch_zero2<T>(p1, p2, pn * B, s), "zero kernel");
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int nb = n_real - r0 < B ? n_real - r0 : B;
-        AMAP_HIP(launch_rotate_scatter<T>(g1, g2, ny, nx, P, seed, (uint64_t)r0, nb, p1, p2, pn, s),
-                 "rotation kernel");
-        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, p1, p2, pn, C, ke, nullptr, pn, false, 0, 0, s,
-                               /*pair_e=*/true));
-        AMAP_HIP(launch_crop2<T>(ke, nullptr, P, ny, nx, kap, nullptr, nb, pn, fn, s), "crop kernel");
+        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, g1, g2, 0, C, kap, nullptr, fn, true, seed, (uint64_t)r0, s,
+                               ny, nx));
         AMAP_HIP(launch_starlet_bc<T>(ny, nx, J, boundary, kap, pl, tmp, nb, fn, (long long)J * fn, s),
                  "bounded starlet kernels");
         AMAP_HIP(launch_welford_bc<T>(pl, (long long)J * fn, nb, M, M2, cnt, r0, s), "statistics kernel");

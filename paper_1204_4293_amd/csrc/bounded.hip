@@ -1,9 +1,8 @@
 // Fields with edges and of any size: the starlet cascade under periodic,
-// mirror or zero boundary rules (0, 1, 2), the zero extension and read-back
-// around the power-of-two KS inversion, the noise realisations' rotation
-// and running statistics (Sec. 1, Sec. 5.1: Welford's update in double,
-// then sigma and S/N), and peak counts with neighbours taken through the
-// edge rule (Sec. 2.2).
+// mirror or zero boundary rules (0, 1, 2), the running statistics of noise
+// realisations (Sec. 1, Sec. 5.1: Welford's update in double, then sigma and
+// S/N), and peak counts with neighbours taken through the edge rule
+// (Sec. 2.2).
 //
 // The a trous cascade is that of Sec. 3 (B3 taps (1,4,6,4,1)/16 at dilation
 // 2^(j-1), row pass along x then column pass along y, w_j = c_{j-1} - c_j);
@@ -143,66 +142,6 @@ k_bc_scale_tile(const T* __restrict__ c_prev, T* __restrict__ w, T* __restrict__
         w[o] = cp - cn;
         c_next[o] = cn;
     }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_pad2(const T* __restrict__ g1, const T* __restrict__ g2, int ny, int nx, int P, T* __restrict__ p1,
-       T* __restrict__ p2) {
-    const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
-    if (x >= P) return;
-    const bool in = y < ny && x < nx;
-    const long long o = (long long)y * P + x, i = (long long)y * nx + x;
-    p1[o] = in ? g1[i] : (T)0;
-    p2[o] = in ? g2[i] : (T)0;
-}
-
-// grid (ceil(nx/256), ny, maps): map z of P x P arrays at + z in_stride,
-// of the ny x nx outputs at + z out_stride
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_crop2(const T* __restrict__ kE_p, const T* __restrict__ kB_p, int P, int nx, T* __restrict__ kE,
-        T* __restrict__ kB, long long in_stride, long long out_stride) {
-    const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
-    if (x >= nx) return;
-    const long long o = blockIdx.z * out_stride + (long long)y * nx + x;
-    const long long i = blockIdx.z * in_stride + (long long)y * P + x;
-    kE[o] = kE_p[i];
-    if (kB) kB[o] = kB_p[i];
-}
-
-// One Philox block (8 flat pixels) per thread: rotate the shears by the
-// phases of realisation r0 + blockIdx.y and scatter them into that
-// realisation's P x P arrays (at + blockIdx.y p_stride).
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_rotate_scatter(const T* __restrict__ g1, const T* __restrict__ g2, int ny, int nx, int P,
-                 uint64_t seed, uint64_t r0, T* __restrict__ p1, T* __restrict__ p2, long long p_stride) {
-    const long long npix = (long long)ny * nx;
-    const long long b = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (8 * b >= npix) return;
-    p1 += blockIdx.y * p_stride;
-    p2 += blockIdx.y * p_stride;
-    uint32_t u[8];
-    philox_block_u32(seed, r0 + blockIdx.y, (uint64_t)b, u);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const long long pix = 8 * b + i;
-        if (pix >= npix) break;
-        const int y = (int)(pix / nx), x = (int)(pix - (long long)y * nx);
-        T a = g1[pix], c = g2[pix];
-        rotate_by_u32(u[i], a, c);
-        p1[(long long)y * P + x] = a;
-        p2[(long long)y * P + x] = c;
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_zero2(T* __restrict__ p1, T* __restrict__ p2, long long count) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
-    p1[i] = (T)0;
-    p2[i] = (T)0;
 }
 
 // Welford's update with realisations r0 .. r0+nb-1 in order, the b-th's
@@ -450,38 +389,7 @@ hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T*
     }
     return hipGetLastError();
 }
-template <typename T>
-hipError_t launch_pad2(const T* g1, const T* g2, int ny, int nx, int P, T* p1, T* p2, hipStream_t s) {
-    AMAP_LAUNCH("pad", s, k_pad2<T><<<dim3((P + 255) / 256, P), 256, 0, s>>>(g1, g2, ny, nx, P, p1, p2));
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_crop2(const T* kE_p, const T* kB_p, int P, int ny, int nx, T* kE, T* kB, int maps,
-                        long long in_stride, long long out_stride, hipStream_t s) {
-    AMAP_LAUNCH("crop", s,
-                k_crop2<T><<<dim3((nx + 255) / 256, ny, maps), 256, 0, s>>>(kE_p, kB_p, P, nx, kE, kB,
-                                                                           in_stride, out_stride));
-    return hipGetLastError();
-}
-
 static unsigned blocks256(long long count) { return (unsigned)((count + 255) / 256); }
-
-template <typename T>
-hipError_t launch_rotate_scatter(const T* g1, const T* g2, int ny, int nx, int P, uint64_t seed,
-                                 uint64_t r0, int nb, T* p1, T* p2, long long p_stride, hipStream_t s) {
-    const long long nblk = ((long long)ny * nx + 7) / 8;
-    AMAP_LAUNCH("rotate_scatter", s,
-                k_rotate_scatter<T><<<dim3(blocks256(nblk), nb), 256, 0, s>>>(g1, g2, ny, nx, P, seed, r0,
-                                                                              p1, p2, p_stride));
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_zero2(T* p1, T* p2, long long count, hipStream_t s) {
-    AMAP_LAUNCH("zero", s, k_zero2<T><<<blocks256(count), 256, 0, s>>>(p1, p2, count));
-    return hipGetLastError();
-}
 
 template <typename T>
 hipError_t launch_welford_bc(const T* w, long long w_stride, int nb, double* M, double* M2,
@@ -500,9 +408,6 @@ hipError_t launch_sigma_snr_bc(const double* M2, int R, const T* w_signal, T* si
 }
 
 #define AMAP_BOUNDED_NOISE(T)                                                                            \
-    template hipError_t launch_rotate_scatter<T>(const T*, const T*, int, int, int, uint64_t, uint64_t,  \
-                                                 int, T*, T*, long long, hipStream_t);                   \
-    template hipError_t launch_zero2<T>(T*, T*, long long, hipStream_t);                                 \
     template hipError_t launch_welford_bc<T>(const T*, long long, int, double*, double*, long long, int, \
                                              hipStream_t);                                               \
     template hipError_t launch_sigma_snr_bc<T>(const double*, int, const T*, T*, T*, long long, hipStream_t);
@@ -514,13 +419,4 @@ template hipError_t launch_starlet_bc<float>(int, int, int, int, const float*, f
                                              long long, long long, hipStream_t);
 template hipError_t launch_starlet_bc<double>(int, int, int, int, const double*, double*, double*, int,
                                               long long, long long, hipStream_t);
-template hipError_t launch_pad2<float>(const float*, const float*, int, int, int, float*, float*,
-                                       hipStream_t);
-template hipError_t launch_pad2<double>(const double*, const double*, int, int, int, double*, double*,
-                                        hipStream_t);
-template hipError_t launch_crop2<float>(const float*, const float*, int, int, int, float*, float*, int,
-                                        long long, long long, hipStream_t);
-template hipError_t launch_crop2<double>(const double*, const double*, int, int, int, double*, double*,
-                                         int, long long, long long, hipStream_t);
-
 }  // namespace amap

@@ -7,11 +7,17 @@
 // inverse transforms):
 //   P1  column strips:  (g1 + i g2) [optionally rotated by Philox phases]
 //                       -> forward FFT along y             -> C
-//   P2  whole rows:     forward FFT along x, multiply by conj(D)/n^2,
-//                       inverse FFT along x                -> C
-//   P3  column strips:  inverse FFT along y -> kappa_E = Re, kappa_B = Im
+//   P2  rows y, -y:     forward FFT along x, multiply by conj(D)/n^2,
+//                       Hermitian part, inverse FFT along x, two columns
+//                       packed into one                    -> half of C
+//   P3  column strips:  inverse FFT along y -> two columns of kappa_E
 // A strip is W adjacent columns, so every HBM access is a W-element row
-// segment; a row pass reads and writes whole rows.
+// segment; a row pass reads whole rows and writes their left halves.
+//
+// Fields that are zero outside an ny x nx rectangle at the grid's origin
+// (CROP) are read and written at their own size: P1 takes only the strips
+// the field reaches, P2 reads and writes only those columns, P3 writes only
+// the field's rows.
 //
 // Each length-N transform is a four-step FFT with N = N1 * N2: every thread
 // holds N1 (then N2) values in registers and runs a radix-2 DFT on them with
@@ -19,300 +25,11 @@
 // LDS exchange separates the two steps.  Along x a transform's N2 threads
 // sit in one wavefront, so the exchange needs no workgroup barrier, and the
 // inverse transform starts from the forward output exactly as each thread
-// holds it.  Float64 from 1024 points, whose per-thread DFTs would not fit
-// the register file, uses radix-4 Stockham passes held in LDS instead.
-#include "amap_device.h"
-#include "amap_launch.h"
-#include "fft_reg.h"
+// holds it.  Transforms whose per-thread DFTs would fill the register file
+// run the three-step kernels of ks_fft3.hip.
+#include "ks_device.h"
 
 namespace amap {
-
-// K consecutive values at p (16-byte aligned) through 16-byte loads.
-template <typename T, int K>
-__device__ __forceinline__ void load16(const T* __restrict__ p, T (&out)[K]) {
-    if constexpr (sizeof(T) == 4) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-        for (int i = 0; i < K / 4; ++i) {
-            const f4 v = reinterpret_cast<const f4*>(p)[i];
-            out[4 * i] = v[0]; out[4 * i + 1] = v[1]; out[4 * i + 2] = v[2]; out[4 * i + 3] = v[3];
-        }
-    } else {
-        typedef double d2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int i = 0; i < K / 2; ++i) {
-            const d2 v = reinterpret_cast<const d2*>(p)[i];
-            out[2 * i] = v[0]; out[2 * i + 1] = v[1];
-        }
-    }
-}
-
-// ---- in-LDS Stockham FFT ---------------------------------------------------
-// Element (line l, index i) of LINES interleaved lines of length 2^LOGN
-// lives at buf[i*IS + l*LS].  NT threads cooperate.  Each stage reads all of
-// a thread's butterfly inputs into registers, synchronises, and writes the
-// outputs in place at their Stockham positions, so one buffer suffices.
-// LINES_FAST picks which index consecutive threads walk (the one with unit
-// stride in LDS, to keep the banks conflict-free on reads).
-template <typename T, int LOGN, int LINES, int NT, int IS, int LS, bool LINES_FAST, bool INV>
-__device__ __forceinline__ void lds_fft(cpx<T>* buf, const cpx<T>* __restrict__ tw) {
-    constexpr int N = 1 << LOGN;
-    const int tid = threadIdx.x;
-    int Ls = 1;
-#pragma unroll
-    for (int st = 0; st < LOGN / 2; ++st) {
-        constexpr int NB = (N / 4) * LINES;
-        constexpr int PER = (NB + NT - 1) / NT;
-        cpx<T> v[PER][4];
-        int base[PER], lo[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int t = tid + q * NT;
-            if (NB % NT == 0 || t < NB) {
-                int l, j;
-                if (LINES_FAST) { l = t % LINES; j = t / LINES; }
-                else            { j = t % (N / 4); l = t / (N / 4); }
-                const int k = j & (Ls - 1);
-                cpx<T> a[4];
-#pragma unroll
-                for (int p = 0; p < 4; ++p) a[p] = buf[(j + p * (N / 4)) * IS + l * LS];
-                if (st > 0) {
-                    const int unit = kMaxN / (4 * Ls);
-#pragma unroll
-                    for (int p = 1; p < 4; ++p) {
-                        const cpx<T> w = tw[p * k * unit];
-                        a[p] = INV ? cmulc(a[p], w) : cmul(a[p], w);
-                    }
-                }
-                const cpx<T> t0 = a[0] + a[2], t1 = a[0] - a[2];
-                const cpx<T> t2 = a[1] + a[3], t3 = rot90<T, INV>(a[1] - a[3]);
-                v[q][0] = t0 + t2;
-                v[q][1] = t1 + t3;
-                v[q][2] = t0 - t2;
-                v[q][3] = t1 - t3;
-                base[q] = (j - k) * 4 + k;
-                lo[q] = l * LS;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int t = tid + q * NT;
-            if (NB % NT == 0 || t < NB) {
-#pragma unroll
-                for (int p = 0; p < 4; ++p) buf[(base[q] + p * Ls) * IS + lo[q]] = v[q][p];
-            }
-        }
-        __syncthreads();
-        Ls *= 4;
-    }
-    if (LOGN & 1) {
-        constexpr int NB = (N / 2) * LINES;
-        constexpr int PER = (NB + NT - 1) / NT;
-        cpx<T> v[PER][2];
-        int base[PER], lo[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int t = tid + q * NT;
-            if (NB % NT == 0 || t < NB) {
-                int l, j;
-                if (LINES_FAST) { l = t % LINES; j = t / LINES; }
-                else            { j = t % (N / 2); l = t / (N / 2); }
-                const int k = j & (Ls - 1);
-                cpx<T> a0 = buf[j * IS + l * LS];
-                cpx<T> a1 = buf[(j + N / 2) * IS + l * LS];
-                if (Ls > 1) {
-                    const cpx<T> w = tw[k * (kMaxN / (2 * Ls))];
-                    a1 = INV ? cmulc(a1, w) : cmul(a1, w);
-                }
-                v[q][0] = a0 + a1;
-                v[q][1] = a0 - a1;
-                base[q] = (j - k) * 2 + k;
-                lo[q] = l * LS;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int t = tid + q * NT;
-            if (NB % NT == 0 || t < NB) {
-                buf[base[q] * IS + lo[q]] = v[q][0];
-                buf[(base[q] + Ls) * IS + lo[q]] = v[q][1];
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// ---- launch geometry ---------------------------------------------------------
-// Column strips: W columns x full height in LDS, at most 128 KiB.
-template <typename T, int LOGN>
-struct StripCfg {
-    static constexpr int N = 1 << LOGN;
-    static constexpr int LDS_ELEMS = (128 * 1024) / (int)sizeof(cpx<T>);
-    static constexpr int W0 = LDS_ELEMS / N;
-    static constexpr int W = W0 > 16 ? 16 : W0;
-    static constexpr int NT0 = (N / 4) * W;
-    static constexpr int NT = NT0 > 512 ? 512 : (NT0 < 64 ? 64 : NT0);
-};
-// Whole rows: ROWS rows per workgroup of NT threads.
-template <typename T, int LOGN>
-struct RowCfg {
-    static constexpr int N = 1 << LOGN;
-    static constexpr int NT = 256;
-    static constexpr int ROWS0 = (4 * NT / N) > 1 ? (4 * NT / N) : 1;
-    static constexpr int ROWS = ROWS0 > N ? N : ROWS0;
-};
-
-__device__ __forceinline__ int signed_freq(int i, int n) { return i < n / 2 ? i : i - n; }
-
-// Reciprocal: the hardware estimate (1 ulp) in single precision, a rounded
-// division in double.
-__device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
-
-// ---- P1: load shears (optionally rotate), forward FFT along y -------------------
-// grid: (n / W strips, batch).  Map b reads g1 + b*g_stride (g_stride = 0 when
-// every batch entry is a noise realisation of the same map) and writes
-// C + b*n*n.  Realisation index r = r0 + b.
-template <typename T, int LOGN, bool ROTATE>
-__global__ void __launch_bounds__((StripCfg<T, LOGN>::NT))
-k_ks_cols_fwd_generic(const T* __restrict__ g1, const T* __restrict__ g2, long long g_stride,
-              const long long* __restrict__ g1_off, const long long* __restrict__ g2_off,
-              cpx<T>* __restrict__ C, uint64_t seed, uint64_t r0,
-              const cpx<T>* __restrict__ tw) {
-    using Cfg = StripCfg<T, LOGN>;
-    constexpr int N = Cfg::N, W = Cfg::W, NT = Cfg::NT;
-    __shared__ cpx<T> buf[N * W];
-    const int b = blockIdx.y;
-    const int x0 = blockIdx.x * W;
-    const T* a1 = g1 + (g1_off ? g1_off[b] : (long long)b * g_stride);
-    const T* a2 = g2 + (g2_off ? g2_off[b] : (long long)b * g_stride);
-    if (ROTATE) {
-        // one Philox block covers 8 consecutive pixels of a row
-        constexpr int OCT_PER_ROW = (W + 7) / 8;
-        const uint64_t r = r0 + b;
-        for (int o = threadIdx.x; o < N * OCT_PER_ROW; o += NT) {
-            const int y = o / OCT_PER_ROW;
-            const int cx = (o % OCT_PER_ROW) * 8;                // column offset in strip
-            const int xa = (W >= 8) ? (x0 + cx) : (x0 & ~7);      // first pixel of the octet
-            const uint64_t pix = (uint64_t)y * N + xa;
-            uint32_t u[8];
-            philox_block_u32(seed, r, pix >> 3, u);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int x = xa + i;
-                if (W < 8 && (x < x0 || x >= x0 + W)) continue;
-                T p = a1[(long long)y * N + x], q = a2[(long long)y * N + x];
-                rotate_by_u32(u[i], p, q);
-                buf[y * W + (x - x0)] = make_cpx(p, q);
-            }
-        }
-    } else {
-        for (int e = threadIdx.x; e < N * W; e += NT) {
-            const int y = e / W, c = e % W;
-            const long long gi = (long long)y * N + x0 + c;
-            buf[e] = make_cpx(a1[gi], a2[gi]);
-        }
-    }
-    __syncthreads();
-    lds_fft<T, LOGN, W, NT, W, 1, true, false>(buf, tw);
-    cpx<T>* out = C + (long long)b * N * N;
-    for (int e = threadIdx.x; e < N * W; e += NT) {
-        const int y = e / W, c = e % W;
-        out[(long long)y * N + x0 + c] = buf[e];
-    }
-}
-
-// ---- P2: rows: forward FFT along x, multiply by conj(D)/n^2, inverse ---------
-template <typename T, int LOGN>
-__global__ void __launch_bounds__((RowCfg<T, LOGN>::NT))
-k_ks_rows_generic(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw) {
-    using Cfg = RowCfg<T, LOGN>;
-    constexpr int N = Cfg::N, NT = Cfg::NT, ROWS = Cfg::ROWS;
-    __shared__ cpx<T> buf[ROWS * N];
-    const int b = blockIdx.y;
-    const int y0 = blockIdx.x * ROWS;
-    cpx<T>* base = C + (long long)b * N * N + (long long)y0 * N;
-    for (int e = threadIdx.x; e < ROWS * N; e += NT) buf[e] = base[e];
-    __syncthreads();
-    lds_fft<T, LOGN, ROWS, NT, 1, N, false, false>(buf, tw);
-    const T inv_n2 = (T)1 / ((T)N * (T)N);
-    for (int e = threadIdx.x; e < ROWS * N; e += NT) {
-        const int m1 = signed_freq(e % N, N);
-        const int m2 = signed_freq(y0 + e / N, N);
-        const int den = m1 * m1 + m2 * m2;
-        cpx<T> v = buf[e];
-        if (den == 0) {
-            v = make_cpx((T)0, (T)0);
-        } else {
-            // conj(D) with D = [(m1^2 - m2^2) + 2 i nu m1 m2] / (m1^2 + m2^2)
-            const bool nyq = (m1 == -N / 2) || (m2 == -N / 2);
-            const T dr = (T)(m1 * m1 - m2 * m2) / (T)den;
-            const T di = nyq ? (T)0 : (T)(2 * m1 * m2) / (T)den;
-            v = make_cpx((v.x * dr + v.y * di) * inv_n2, (v.y * dr - v.x * di) * inv_n2);
-        }
-        buf[e] = v;
-    }
-    __syncthreads();
-    lds_fft<T, LOGN, ROWS, NT, 1, N, false, true>(buf, tw);
-    for (int e = threadIdx.x; e < ROWS * N; e += NT) base[e] = buf[e];
-}
-
-// ---- P3: inverse FFT along y, split real/imaginary ---------------------------
-template <typename T, int LOGN>
-__global__ void __launch_bounds__((StripCfg<T, LOGN>::NT))
-k_ks_cols_inv_generic(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ kB,
-              long long out_stride, const long long* __restrict__ kE_off, const cpx<T>* __restrict__ tw) {
-    using Cfg = StripCfg<T, LOGN>;
-    constexpr int N = Cfg::N, W = Cfg::W, NT = Cfg::NT;
-    __shared__ cpx<T> buf[N * W];
-    const int b = blockIdx.y;
-    const int x0 = blockIdx.x * W;
-    const cpx<T>* in = C + (long long)b * N * N;
-    for (int e = threadIdx.x; e < N * W; e += NT) {
-        const int y = e / W, c = e % W;
-        buf[e] = in[(long long)y * N + x0 + c];
-    }
-    __syncthreads();
-    lds_fft<T, LOGN, W, NT, W, 1, true, true>(buf, tw);
-    T* oe = kE + (kE_off ? kE_off[b] : (long long)b * out_stride);
-    T* ob = kB ? kB + (long long)b * out_stride : nullptr;
-    for (int e = threadIdx.x; e < N * W; e += NT) {
-        const int y = e / W, c = e % W;
-        const long long gi = (long long)y * N + x0 + c;
-        oe[gi] = buf[e].x;
-        if (ob) ob[gi] = buf[e].y;
-    }
-}
-
-// exp(-+2 pi i e / N) from the 4096-entry table
-template <typename T, int LOGN, bool INV>
-__device__ __forceinline__ cpx<T> table_twiddle(const cpx<T>* __restrict__ tw, int e) {
-    const cpx<T> w = tw[(e & ((1 << LOGN) - 1)) << (kMaxLogN - LOGN)];
-    return INV ? make_cpx(w.x, -w.y) : w;
-}
-
-// exp(-+2 pi i base k / N) for k = 1 .. K-1, passed to f(k, w) in increasing
-// k: five table reads (base times 1, 2, 4, 8, 16) and one complex product
-// per power, w(k) = w(k without its lowest set bit) * w(lowest set bit), so
-// each power carries at most four roundings and only a few are live at once.
-template <typename T, int LOGN, bool INV, int K, typename Fn>
-__device__ __forceinline__ void twiddle_powers(const cpx<T>* __restrict__ tw, int base, Fn&& f) {
-    static_assert(K <= 64, "at most 64 powers");
-    constexpr int NB = K <= 2 ? 1 : (K <= 4 ? 2 : (K <= 8 ? 3 : (K <= 16 ? 4 : (K <= 32 ? 5 : 6))));
-    cpx<T> p[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) p[b] = table_twiddle<T, LOGN, INV>(tw, base << b);
-    cpx<T> w[K];
-#pragma unroll
-    for (int k = 1; k < K; ++k) {
-        const int low = k & -k, rest = k - low;
-        const int bit = __builtin_ctz(low);
-        w[k] = rest ? cmul(w[rest], p[bit]) : p[bit];
-        f(k, w[k]);
-    }
-}
 
 // Four-step factors: N = N1 * N2, N1 = N2 or 2 N2.
 template <int LOGN>
@@ -358,24 +75,6 @@ using StripF = Strip4<T, LOGN, true, WREQ>;
 template <typename T, int LOGN, int WREQ = 0>
 using StripI = Strip4<T, LOGN, false, WREQ>;
 
-// Strip s and map b of the column kernels' workgroup.  With `xcd` set,
-// workgroups are renumbered so that consecutive strips of a map run on one
-// XCD (the hardware deals workgroups out to the eight XCDs in turn): strips
-// whose row segments share a cache line then meet in one L2 instead of each
-// XCD fetching the whole line.  Not used where all maps read one shared
-// input (noise realisations), which each XCD keeps in its L2 as it is.
-__device__ __forceinline__ void strip_of(int xcd, int& s, int& b) {
-    s = blockIdx.x;
-    b = blockIdx.y;
-    const int nx = gridDim.x;
-    const int total = nx * gridDim.y;
-    if (xcd && (total & 7) == 0) {
-        const int l = blockIdx.x + nx * blockIdx.y;
-        const int v = (l & 7) * (total >> 3) + (l >> 3);
-        s = v % nx;
-        b = v / nx;
-    }
-}
 template <typename T, int LOGN>
 struct Row4 {
     static constexpr int N2 = FS<LOGN>::N2, N1 = FS<LOGN>::N1;
@@ -387,19 +86,15 @@ struct Row4 {
     static constexpr int EX = (N1 * (N2 + 1)) > (N2 * (N1 + 1)) ? (N1 * (N2 + 1)) : (N2 * (N1 + 1));
 };
 
-// Orders the LDS accesses of one wavefront (the lanes of one transform).
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 // ---- P1: load shears (optionally rotate), forward FFT along y (four-step) -------
-template <typename T, int LOGN, bool ROTATE, int WREQ>
+// CROP: the shears are ny x nx, row-major, zero outside; only the strips they
+// reach run.
+template <typename T, int LOGN, bool ROTATE, bool CROP, int WREQ>
 __global__ void __launch_bounds__((StripF<T, LOGN, WREQ>::NT), (StripF<T, LOGN, WREQ>::MINW))
 k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_stride,
               const long long* __restrict__ g1_off, const long long* __restrict__ g2_off,
               cpx<T>* __restrict__ C, uint64_t seed, uint64_t r0, const cpx<T>* __restrict__ tw,
-              int xcd) {
+              int xcd, int ny, int nx) {
     using F = FS<LOGN>;
     using S = StripF<T, LOGN, WREQ>;
     constexpr int N = F::N, N1 = F::N1, N2 = F::N2, W = S::W, NT = S::NT, PH = S::PH;
@@ -418,8 +113,49 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
 #pragma unroll
     for (int p = 0; p < PH; ++p) {
         const int y0 = p * ROWS;
+        if (CROP && y0 >= ny) {  // rows outside the field
+#pragma unroll
+            for (int n1 = 0; n1 < K; ++n1) a[p * K + n1] = make_cpx((T)0, (T)0);
+            continue;
+        }
         if (p > 0) __syncthreads();  // the previous phase's reads are done
-        if (ROTATE) {
+        if constexpr (CROP) {
+            const int wv = nx - x0 < W ? nx - x0 : W;              // the field's columns and
+            const int yv = ny - y0 < ROWS ? ny - y0 : ROWS;        // rows in this phase
+            if (wv < W || yv < ROWS) {
+                for (int e = threadIdx.x; e < ROWS * W; e += NT) buf[e] = make_cpx((T)0, (T)0);
+                __syncthreads();
+            }
+            if constexpr (ROTATE) {
+                // Philox blocks cover 8 pixels in flat order: a row segment
+                // meets up to W / 8 + 1 of them
+                constexpr int OCT = (W + 6) / 8 + 1;
+                const uint64_t r = r0 + b;
+                for (int o = threadIdx.x; o < yv * OCT; o += NT) {
+                    const int yl = o / OCT;
+                    const int f0 = (y0 + yl) * nx + x0;            // flat index of the segment
+                    const int oct = (f0 >> 3) + (o - yl * OCT);
+                    if (8 * oct >= f0 + wv) continue;
+                    uint32_t u[8];
+                    philox_block_u32(seed, r, (uint64_t)oct, u);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int f = 8 * oct + i;
+                        if (f < f0 || f >= f0 + wv) continue;
+                        T gp = a1[f], gq = a2[f];
+                        rotate_by_u32(u[i], gp, gq);
+                        buf[yl * W + (f - f0)] = make_cpx(gp, gq);
+                    }
+                }
+            } else {
+                for (int e = threadIdx.x; e < yv * W; e += NT) {
+                    const int yl = e / W, cc = e % W;
+                    if (cc >= wv) continue;
+                    const int gi = (y0 + yl) * nx + x0 + cc;
+                    buf[e] = make_cpx(a1[gi], a2[gi]);
+                }
+            }
+        } else if (ROTATE) {
             // one Philox block covers 8 consecutive pixels of a row
             constexpr int OCT_PER_ROW = (W + 7) / 8;
             const uint64_t r = r0 + b;
@@ -487,17 +223,19 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
 // ---- P2: rows: forward FFT along x, multiply by conj(D)/n^2, inverse (four-step) -
 // The forward transform of one row for the N2 lanes t of a line, with E its
 // exchange region: on return b[r][k2] holds the row's transform at
-// frequency k1 + N1 k2, k1 = t + N2 r.
-template <typename T, int LOGN>
+// frequency k1 + N1 k2, k1 = t + N2 r.  CROP: the row is zero from x = nx on
+// (and not read there).
+template <typename T, int LOGN, bool CROP>
 __device__ __forceinline__ void ks_row_spectrum(const cpx<T>* __restrict__ row, int t, cpx<T>* E,
                                                 const cpx<T>* __restrict__ tw,
-                                                cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::N2]) {
+                                                cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::N2], int nx) {
     using F = FS<LOGN>;
     constexpr int N1 = F::N1, N2 = F::N2, RR = F::RR;
     cpx<T> a[N1];
     // forward, step 1: DFT_N1 over n1 of x[N2 n1 + t]
 #pragma unroll
-    for (int n1 = 0; n1 < N1; ++n1) a[n1] = row[N2 * n1 + t];
+    for (int n1 = 0; n1 < N1; ++n1)
+        a[n1] = !CROP || N2 * n1 + t < nx ? row[N2 * n1 + t] : make_cpx((T)0, (T)0);
     dft_reg<T, N1, false>(a);
     E[t] = a[0];
     twiddle_powers<T, LOGN, false, N1>(tw, t, [&](int k1, const cpx<T>& w) {
@@ -546,90 +284,35 @@ __device__ __forceinline__ void ks_multiply(cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::
     }
 }
 
-// The forward half of one spectral row y: transform, then times
-// conj(D)/(SCALE_DEN n^2).
-template <typename T, int LOGN, int SCALE_DEN = 1>
-__device__ __forceinline__ void ks_row_forward(const cpx<T>* __restrict__ row, int y, int t,
-                                               cpx<T>* E, const cpx<T>* __restrict__ tw,
-                                               cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::N2]) {
-    ks_row_spectrum<T, LOGN>(row, t, E, tw, b);
-    ks_multiply<T, LOGN, SCALE_DEN>(b, y, t);
-}
-
-// The inverse half: from b[r][k2] at frequency k1 + N1 k2 (k1 = t + N2 r),
-// on return a[n] holds the row's inverse transform at x = t + N2 n.
+// P2 packed.  kappa_E is the inverse transform of the Hermitian part
+// H(k) = [K(k) + conj(K(-k))]/2 of the spectrum K (kappa_B that of
+// [K(k) - conj(K(-k))]/2i).  Transformed back along x, H gives complex rows
+// h(ky, x) with h(-ky, x) = conj(h(ky, x)): half of them carry everything,
+// and since kappa_E is real, columns 2c and 2c+1 can share one inverse
+// transform along y, of z(ky, c) = h(ky, 2c) + i h(ky, 2c+1) (real part:
+// column 2c, imaginary part: column 2c+1).  So a map's packed spectrum is
+// n x n/2 (the left half of its rows; kappa_B's, where wanted, takes the
+// right half), and without kappa_B the row pass writes and the inverse
+// column pass reads half of the full spectrum.  kappa_E does not depend on
+// whether kappa_B is wanted.
+//
+// A unit takes spectral rows y and -y: two lines run the forward transform
+// and the multiply and leave their spectral rows in LDS in natural frequency
+// order (-k is the mirrored address).  H(y, .) is then transformed back by
+// all 2 N2 lanes of the unit (the lanes of row y, then those of row -y):
+// the low half holds the even-indexed and the high half the odd-indexed
+// inputs of each length-N2 and length-N1 DFT of the four-step inverse, and
+// one radix-2 step across the halves completes them.  Neighbouring lanes end
+// with neighbouring columns: the even lane forms z(y, .), the odd one
+// z(-y, .), over the first halves of the rows they read.  Rows 0 and n/2
+// are their own mirrors; their h are real and share one transform as real
+// and imaginary part.
 template <typename T, int LOGN>
-__device__ __forceinline__ void ks_row_inverse(cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::N2], int t,
-                                               cpx<T>* E, const cpx<T>* __restrict__ tw,
-                                               cpx<T> (&a)[FS<LOGN>::N1]) {
-    using F = FS<LOGN>;
-    constexpr int N1 = F::N1, N2 = F::N2, RR = F::RR;
-    wave_lds_sync();  // earlier reads of the exchange region are done before it is reused
-    // inverse, step 1: DFT_N2 over k2 for each k1 held, twiddle, exchange
-#pragma unroll
-    for (int r = 0; r < RR; ++r) {
-        const int k1 = t + N2 * r;
-        dft_reg<T, N2, true>(b[r]);
-        E[k1] = b[r][0];
-        twiddle_powers<T, LOGN, true, N2>(tw, k1, [&](int m, const cpx<T>& w) {
-            E[m * (N1 + 1) + k1] = cmul(b[r][m], w);
-        });
-    }
-    wave_lds_sync();
-    // inverse, step 2: DFT_N1 over k1 for m = t -> x[t + N2 n]
-#pragma unroll
-    for (int k1 = 0; k1 < N1; ++k1) a[k1] = E[t * (N1 + 1) + k1];
-    dft_reg<T, N1, true>(a);
-}
-
-// The whole row: forward, multiply, inverse.
-template <typename T, int LOGN>
-__device__ __forceinline__ void ks_row_line(const cpx<T>* __restrict__ row, int y, int t,
-                                            cpx<T>* E, const cpx<T>* __restrict__ tw,
-                                            cpx<T> (&a)[FS<LOGN>::N1]) {
-    cpx<T> b[FS<LOGN>::RR][FS<LOGN>::N2];
-    ks_row_forward<T, LOGN>(row, y, t, E, tw, b);
-    ks_row_inverse<T, LOGN>(b, t, E, tw, a);
-}
-
-template <typename T, int LOGN>
-__global__ void __launch_bounds__((Row4<T, LOGN>::NT))
-k_ks_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw) {
-    using F = FS<LOGN>;
-    using R4 = Row4<T, LOGN>;
-    constexpr int N = F::N, N1 = F::N1, N2 = F::N2;
-    __shared__ cpx<T> ex[R4::LINES * R4::EX];
-    const int line = threadIdx.x / N2, t = threadIdx.x % N2;
-    if (line >= R4::LINES) return;  // no workgroup barrier follows
-    const int y = blockIdx.x * R4::LINES + line;
-    cpx<T>* row = C + (long long)blockIdx.y * N * N + (long long)y * N;
-    cpx<T> a[N1];
-    ks_row_line<T, LOGN>(row, y, t, ex + line * R4::EX, tw, a);
-#pragma unroll
-    for (int n = 0; n < N1; ++n) row[t + N2 * n] = a[n];
-}
-
-// P2 for pairs of maps whose kappa_B is not wanted.  kappa_E of a map is
-// the inverse transform of the Hermitian part H(k) = [K(k) + conj(K(-k))]/2
-// of its spectrum K, which is real; two maps a, b then share one inverse
-// transform, of Z = H_a + i H_b, whose real and imaginary parts are their
-// kappa_E.  A workgroup unit takes spectral rows y and -y (rows 0 and n/2
-// are their own partners) of both maps: four lines, one per (map, row),
-// run the forward transform and the multiply and leave their spectral rows
-// in LDS in natural frequency order (-k is the mirrored address).  The two
-// Z rows, y and -y, are then transformed back by two lane groups of 2 N2
-// lanes each (the lanes of map a, then those of map b), so every lane does
-// the same work: within a group the low half holds the even-indexed and the
-// high half the odd-indexed inputs of each length-N2 and length-N1 DFT of
-// the four-step inverse, and one radix-2 step across the halves completes
-// them.  The group writes its Z row over map a's row.  Pair p holds maps 2p
-// and 2p+1 (map 2p alone, read twice, if 2p+1 = batch).
-template <typename T, int LOGN>
-struct RowPair {
+struct RowHalf {
     static constexpr int N2 = FS<LOGN>::N2, N = 1 << LOGN;
-    static constexpr int U0 = 128 / (4 * N2) > 0 ? 128 / (4 * N2) : 1;
+    static constexpr int U0 = 64 / (2 * N2);  // one wavefront: small maps spread over more CUs
     static constexpr int UNITS = U0 > N / 2 ? N / 2 : U0;  // row pairs per workgroup
-    static constexpr int NT = UNITS * 4 * N2;
+    static constexpr int NT = UNITS * 2 * N2;
 };
 
 // Exchange across the halves of a group of 2 H lanes (H a power of two, the
@@ -745,33 +428,35 @@ __device__ __forceinline__ void ks_multiply_pair(cpx<T> (&b)[FS<LOGN>::RR][FS<LO
     }
 }
 
-template <typename T, int LOGN>
-__global__ void __launch_bounds__((RowPair<T, LOGN>::NT))
-k_ks_rows_pair(cpx<T>* __restrict__ C, int batch, const cpx<T>* __restrict__ tw) {
+template <typename T, int LOGN, bool WANT_B, bool CROP>
+__global__ void __launch_bounds__((RowHalf<T, LOGN>::NT))
+k_ks_rows_half(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
     using F = FS<LOGN>;
-    using RP = RowPair<T, LOGN>;
+    using RP = RowHalf<T, LOGN>;
     constexpr int N = F::N, N1 = F::N1, N2 = F::N2, RR = F::RR, EX = Row4<T, LOGN>::EX;
     constexpr int M2 = N2 / 2, M1 = N1 / 2;  // values per lane in the two inverse steps
-    // a lane group (2 N2 lanes, aligned) lies in one wavefront, so wave-level
-    // ordering covers its exchange and its cross-lane steps
-    static_assert(2 * N2 <= 64, "a lane group must lie in one wavefront");
+    // a unit (2 N2 lanes, aligned) lies in one wavefront, so wave-level
+    // ordering covers its exchanges and its cross-lane steps
+    static_assert(2 * N2 <= 64, "a unit must lie in one wavefront");
     static_assert(N2 >= 4, "at least two values per lane and half");
-    __shared__ cpx<T> ex[RP::UNITS * 4 * EX];
+    // the exchange of the inverse takes the spectra's place, or, where
+    // kappa_B is formed from them afterwards, a region of its own
+    constexpr int REG = WANT_B ? 3 : 2;
+    __shared__ cpx<T> ex[RP::UNITS * REG * EX];
     const int line = threadIdx.x / N2, t = threadIdx.x % N2;
-    const int u = line >> 2, role = line & 3;  // role: map (role >> 1), row (role & 1)
+    const int u = line >> 1, h = line & 1;  // h: row y (0) or -y (1)
+    const bool hi = h != 0;
     const int q = blockIdx.x * RP::UNITS + u;
     const int r0 = q, r1 = q == 0 ? N / 2 : N - q;
-    const int ma = 2 * blockIdx.y;
-    const int mb = ma + 1 < batch ? ma + 1 : ma;
+    cpx<T>* map = C + (long long)blockIdx.y * N * N;
     {
-        const int y = (role & 1) ? r1 : r0;
-        const cpx<T>* row = C + (long long)((role >> 1) ? mb : ma) * N * N + (long long)y * N;
-        cpx<T>* E = ex + line * EX;
+        const int y = hi ? r1 : r0;
+        cpx<T>* E = ex + (u * REG + h) * EX;
         cpx<T> b[RR][N2];
-        ks_row_spectrum<T, LOGN>(row, t, E, tw, b);
+        ks_row_spectrum<T, LOGN, CROP>(map + (long long)y * N, t, E, tw, b, nx);
         // times conj(D), carrying the 1/2 of H; rows 0 and n/2 are not a
         // conjugate pair
-        if (q != 0) ks_multiply_pair<T, LOGN, 2>(b, r0, t, (role & 1) != 0);
+        if (q != 0) ks_multiply_pair<T, LOGN, 2>(b, r0, t, hi);
         else ks_multiply<T, LOGN, 2>(b, y, t);
         wave_lds_sync();  // the forward exchange's reads are done
 #pragma unroll
@@ -779,81 +464,88 @@ k_ks_rows_pair(cpx<T>* __restrict__ C, int batch, const cpx<T>* __restrict__ tw)
 #pragma unroll
             for (int k2 = 0; k2 < N2; ++k2) E[t + N2 * r + N1 * k2] = b[r][k2];
     }
-    // inverse: group g = role >> 1 transforms Z row y_g (slot g); h = role & 1
-    const int g = role >> 1, h = role & 1;
-    const bool hi = h != 0;
-    const int yg = g ? r1 : r0;
-    const int pg = q == 0 ? g : 1 - g;  // slot of row -y_g
     // inter-step twiddles exp(2 pi i k1 m / N) for this lane's k1 and m
     cpx<T> w[RR][M2];
 #pragma unroll
     for (int r = 0; r < RR; ++r)
 #pragma unroll
         for (int j = 0; j < M2; ++j) w[r][j] = table_twiddle<T, LOGN, true>(tw, (t + N2 * r) * pair_out<M2>(j, h));
-    __syncthreads();  // the four spectral rows of every unit are in LDS (and C's rows read)
-    // Z = H_a + i H_b at k1 = t + N2 r, k2 = 2 j + h (the spectra carry the 1/2)
-    const cpx<T>* base = ex + (u * 4) * EX;
-    const cpx<T>* Ka = base + g * EX;
-    const cpx<T>* Kap = base + pg * EX;
-    const cpx<T>* Kb = base + (2 + g) * EX;
-    const cpx<T>* Kbp = base + (2 + pg) * EX;
-    cpx<T> z[RR][M2];
+    wave_lds_sync();  // the unit's two spectral rows are in LDS
+    // H at k1 = t + N2 r, k2 = 2 j + h (the spectra carry the 1/2)
+    const cpx<T>* Ka = ex + (u * REG) * EX;
+    const cpx<T>* Kb = ex + (u * REG + 1) * EX;
+    cpx<T>* E = ex + (u * REG + (WANT_B ? 2 : 0)) * EX;  // the unit's exchange region
+    const bool odd = (t & 1) != 0;
 #pragma unroll
-    for (int r = 0; r < RR; ++r)
+    for (int f = 0; f < (WANT_B ? 2 : 1); ++f) {  // kappa_E, kappa_B
+        cpx<T> z[RR][M2];
 #pragma unroll
-        for (int j = 0; j < M2; ++j) {
-            const int kx = t + N2 * r + N1 * (2 * j + h), mk = (N - kx) & (N - 1);
-            const cpx<T> ka = Ka[kx], kap = Kap[mk], kb = Kb[kx], kbp = Kbp[mk];
-            const T har = ka.x + kap.x, hai = ka.y - kap.y;
-            const T hbr = kb.x + kbp.x, hbi = kb.y - kbp.y;
-            z[r][j] = make_cpx(har - hbi, hai + hbr);
+        for (int r = 0; r < RR; ++r)
+#pragma unroll
+            for (int j = 0; j < M2; ++j) {
+                const int kx = t + N2 * r + N1 * (2 * j + h), mk = (N - kx) & (N - 1);
+                if (q != 0) {
+                    z[r][j] = hermitian(Ka[kx], Kb[mk], f != 0);
+                } else {  // H_0 + i H_{n/2}
+                    const cpx<T> ha = hermitian(Ka[kx], Ka[mk], f != 0), hb = hermitian(Kb[kx], Kb[mk], f != 0);
+                    z[r][j] = make_cpx(ha.x - hb.y, ha.y + hb.x);
+                }
+            }
+        // step 1: DFT_N2 over k2 for each k1 held, then the twiddle
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+            pair_dft_inv<T, M2, N2>(z[r], hi);
+#pragma unroll
+            for (int j = 0; j < M2; ++j) z[r][j] = cmul(z[r][j], w[r][j]);
         }
-    // step 1: DFT_N2 over k2 for each k1 held, then the twiddle
+        wave_lds_sync();  // the reads of the spectra are done
 #pragma unroll
-    for (int r = 0; r < RR; ++r) {
-        pair_dft_inv<T, M2, N2>(z[r], hi);
+        for (int r = 0; r < RR; ++r)
 #pragma unroll
-        for (int j = 0; j < M2; ++j) z[r][j] = cmul(z[r][j], w[r][j]);
+            for (int j = 0; j < M2; ++j) E[pair_out<M2>(j, h) * (N1 + 1) + t + N2 * r] = z[r][j];
+        wave_lds_sync();
+        // step 2: DFT_N1 over k1 for m = t -> h(y, t + N2 n)
+        cpx<T> v[M1];
+#pragma unroll
+        for (int j = 0; j < M1; ++j) v[j] = E[t * (N1 + 1) + 2 * j + h];
+        pair_dft_inv<T, M1, N2>(v, hi);
+        cpx<T>* out = map + (long long)(odd ? r1 : r0) * N + f * (N / 2) + (t >> 1);
+#pragma unroll
+        for (int j = 0; j < M1; ++j) {
+            const cpx<T> z = pack_columns(v[j], odd, q == 0);
+            const int xc = (N2 / 2) * pair_out<M1>(j, h);  // column pair, from t / 2
+            if (!CROP || 2 * (xc + (t >> 1)) < nx) out[xc] = z;
+        }
     }
-    __syncthreads();  // every group's reads of the spectra are done
-    cpx<T>* E = ex + (u * 4 + 2 * g) * EX;  // this group's exchange region
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-#pragma unroll
-        for (int j = 0; j < M2; ++j) E[pair_out<M2>(j, h) * (N1 + 1) + t + N2 * r] = z[r][j];
-    wave_lds_sync();
-    // step 2: DFT_N1 over k1 for m = t -> x[t + N2 n]
-    cpx<T> v[M1];
-#pragma unroll
-    for (int j = 0; j < M1; ++j) v[j] = E[t * (N1 + 1) + 2 * j + h];
-    pair_dft_inv<T, M1, N2>(v, hi);
-    cpx<T>* out = C + (long long)ma * N * N + (long long)yg * N;
-#pragma unroll
-    for (int j = 0; j < M1; ++j) out[t + N2 * pair_out<M1>(j, h)] = v[j];
 }
 
-// ---- P3: inverse FFT along y (four-step), split real/imaginary -----------------
-template <typename T, int LOGN, int WREQ>
+// ---- P3: inverse FFT along y (four-step), two columns a transform -----------------
+// Column c < n/2 of the packed spectra becomes columns 2c (real part) and
+// 2c + 1 (imaginary part) of kappa_E, column n/2 + c those of kappa_B.  The
+// grid has `strips` strips for each of them.  CROP: ny x nx outputs.
+template <typename T, int LOGN, bool CROP, int WREQ>
 __global__ void __launch_bounds__((StripI<T, LOGN, WREQ>::NT), (StripI<T, LOGN, WREQ>::MINW))
-k_ks_cols_inv(const cpx<T>* __restrict__ C, long long in_stride, T* __restrict__ kE,
-              T* __restrict__ kB, long long out_stride, int kB_count,
-              const long long* __restrict__ kE_off, const cpx<T>* __restrict__ tw, int xcd) {
+k_ks_cols_inv(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ kB,
+              long long out_stride, const long long* __restrict__ kE_off, const cpx<T>* __restrict__ tw,
+              int xcd, int strips, int ny, int nx) {
     using F = FS<LOGN>;
     using S = StripI<T, LOGN, WREQ>;
     constexpr int N = F::N, N1 = F::N1, N2 = F::N2, W = S::W, PH = S::PH, K = N1 / PH;
     __shared__ cpx<T> buf[S::LDS];
     int sx, b;
     strip_of(xcd, sx, b);
-    const int x0 = sx * W;
+    const bool second = sx >= strips;  // kappa_B
     const int c = threadIdx.x % W, t = threadIdx.x / W;
-    const cpx<T>* in = C + (long long)b * in_stride + x0 + c;
+    const int col = (second ? sx - strips : sx) * W + c;
+    const cpx<T>* in = C + (long long)b * N * N + (second ? N / 2 : 0) + col;
     cpx<T> a[N1];
 #pragma unroll
     for (int n1 = 0; n1 < N1; ++n1) a[n1] = in[(long long)(N2 * n1 + t) * N];
     dft_reg<T, N1, true>(a);
     twiddle_powers<T, LOGN, true, N1>(tw, t, [&](int k1, const cpx<T>& w) { a[k1] = cmul(a[k1], w); });
-    T* oe = kE + (kE_off ? kE_off[b] : (long long)b * out_stride) + x0 + c;
-    T* ob = (kB && b < kB_count) ? kB + (long long)b * out_stride + x0 + c : nullptr;
+    const int os = CROP ? nx : N;  // output row
+    T* o = (second ? kB + (long long)b * out_stride
+                   : kE + (kE_off ? kE_off[b] : (long long)b * out_stride)) + 2 * col;
     // exchange in PH phases of K first-step outputs each, as the forward pass
 #pragma unroll
     for (int q = 0; q < PH; ++q) {
@@ -872,9 +564,14 @@ k_ks_cols_inv(const cpx<T>* __restrict__ C, long long in_stride, T* __restrict__
                 const int k1 = q * K + kl;
 #pragma unroll
                 for (int k2 = 0; k2 < N2; ++k2) {
-                    const long long gi = (long long)(k1 + N1 * k2) * N;
-                    oe[gi] = v[k2].x;
-                    if (ob) ob[gi] = v[k2].y;
+                    const int y = k1 + N1 * k2;
+                    if constexpr (CROP) {
+                        if (y >= ny) continue;
+                        if (2 * col < nx) o[(long long)y * os] = v[k2].x;
+                        if (2 * col + 1 < nx) o[(long long)y * os + 1] = v[k2].y;
+                    } else {
+                        *reinterpret_cast<cpx<T>*>(o + (long long)y * os) = v[k2];
+                    }
                 }
             }
         }
@@ -882,119 +579,159 @@ k_ks_cols_inv(const cpx<T>* __restrict__ C, long long in_stride, T* __restrict__
 }
 
 // ---- host launchers ------------------------------------------------------------
-// Double-precision transforms from 1024 points keep their data in LDS (their
-// per-thread DFTs would not fit the register file); everything else runs the
-// four-step register kernels.
-template <typename T, int LOGN>
-constexpr bool use_generic() { return sizeof(T) == 8 && LOGN >= 10; }
-
-// Pairs of maps share the inverse transform where the four-step kernels run
-// and the four exchange rows of a unit fit 128 KiB of LDS (as the row pass's
-// four rows do): up to n = 2048 in float32.
-template <typename T, int LOGN>
-constexpr bool pair_ok() {
-    return !use_generic<T, LOGN>() && 2 * FS<LOGN>::N2 <= 64 &&
-           (size_t)RowPair<T, LOGN>::UNITS * 4 * Row4<T, LOGN>::EX * sizeof(cpx<T>) <= 128 * 1024;
+// Strips as wide as leave a launch ~512 workgroups (cols columns of each of
+// `maps` maps), from wmax down to 4 columns (n = 256 and up: narrower maps
+// are small at any width).
+static int strip_width(int n, int cols, long long maps, int wmax) {
+    int w = wmax;
+    while (n >= 256 && w > 4 && (cols + w - 1) / w * maps < 512) w /= 2;
+    return w;
 }
 
-// The four-step kernels with strips of WREQ columns.
-template <typename T, int LOGN, int WREQ>
-static hipError_t ks_launch_w(const KsArgs<T>& a) {
+template <typename T, int LOGN, bool CROP, int WREQ>
+static hipError_t cols_fwd_w(const KsArgs<T>& a) {
     constexpr int N = 1 << LOGN;
-    using SF = StripF<T, LOGN, WREQ>;
-    using SI = StripI<T, LOGN, WREQ>;
-    using R = Row4<T, LOGN>;
-    const dim3 gf(N / SF::W, a.batch), gi(N / SI::W, a.batch), gr(N / R::LINES, a.batch);
-    // XCD grouping where strips read or write row segments narrower than a
-    // 128-byte line, except for a shared input (noise realisations)
+    using S = StripF<T, LOGN, WREQ>;
+    const int nx = CROP ? a.nx : N, ny = CROP ? a.ny : N;
+    const dim3 g((nx + S::W - 1) / S::W, a.batch);
+    // XCD grouping where strips read row segments narrower than a 128-byte
+    // line, except for a shared input (noise realisations), whose lines each
+    // XCD's strips keep in its L2 as they are dealt out (grouped by strip it
+    // measured 4 to 6% slower at 1024^2 and 2048^2)
     const bool shared_in = a.g_stride == 0 && !a.g1_off && a.batch > 1;
-    const int xcd_in = (!shared_in && SF::W * (int)sizeof(T) < 128) ? 1 : 0;
-    const int xcd_out = SI::W * (int)sizeof(T) < 128 ? 1 : 0;
+    const int xcd = (!shared_in && S::W * (int)sizeof(T) < 128) ? 1 : 0;
     if (a.rotate)
         AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
-                    k_ks_cols_fwd<T, LOGN, true, WREQ><<<gf, SF::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd_in));
+                    k_ks_cols_fwd<T, LOGN, true, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
+                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
     else
         AMAP_LAUNCH("ks_cols_fwd", a.stream,
-                    k_ks_cols_fwd<T, LOGN, false, WREQ><<<gf, SF::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd_in));
-    if constexpr (pair_ok<T, LOGN>()) {
-        if (a.pair_e) {
-            using RP = RowPair<T, LOGN>;
-            if (a.kE_off || a.batch < 1) return hipErrorInvalidValue;
-            const int pairs = (a.batch + 1) / 2;
-            AMAP_LAUNCH("ks_rows_pair", a.stream,
-                        k_ks_rows_pair<T, LOGN><<<dim3((N / 2) / RP::UNITS, pairs), RP::NT, 0, a.stream>>>(
-                            a.C, a.batch, a.tw));
-            AMAP_LAUNCH("ks_cols_inv_pair", a.stream,
-                        k_ks_cols_inv<T, LOGN, WREQ><<<dim3(N / SI::W, pairs), SI::NT, 0, a.stream>>>(
-                            a.C, 2ll * N * N, a.kE, a.kE + a.out_stride, 2 * a.out_stride,
-                            a.batch / 2, nullptr, a.tw, xcd_out));
-            return hipGetLastError();
-        }
-    }
-    AMAP_LAUNCH("ks_rows", a.stream, k_ks_rows<T, LOGN><<<gr, R::NT, 0, a.stream>>>(a.C, a.tw));
-    AMAP_LAUNCH("ks_cols_inv", a.stream,
-                k_ks_cols_inv<T, LOGN, WREQ><<<gi, SI::NT, 0, a.stream>>>(
-                    a.C, (long long)N * N, a.kE, a.pair_e ? nullptr : a.kB, a.out_stride, a.batch,
-                    a.kE_off, a.tw, xcd_out));
+                    k_ks_cols_fwd<T, LOGN, false, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
+                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
     return hipGetLastError();
 }
 
-template <typename T, int LOGN>
-static hipError_t ks_launch_n(const KsArgs<T>& a) {
-    constexpr int N = 1 << LOGN;
-    if constexpr (use_generic<T, LOGN>()) {
-        using S = StripCfg<T, LOGN>;
-        using R = RowCfg<T, LOGN>;
-        const dim3 gs(N / S::W, a.batch), gr(N / R::ROWS, a.batch);
-        if (a.rotate)
-            AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
-                        k_ks_cols_fwd_generic<T, LOGN, true><<<gs, S::NT, 0, a.stream>>>(
-                            a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw));
-        else
-            AMAP_LAUNCH("ks_cols_fwd", a.stream,
-                        k_ks_cols_fwd_generic<T, LOGN, false><<<gs, S::NT, 0, a.stream>>>(
-                            a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw));
-        AMAP_LAUNCH("ks_rows", a.stream,
-                    k_ks_rows_generic<T, LOGN><<<gr, R::NT, 0, a.stream>>>(a.C, a.tw));
-        AMAP_LAUNCH("ks_cols_inv", a.stream,
-                    k_ks_cols_inv_generic<T, LOGN><<<gs, S::NT, 0, a.stream>>>(a.C, a.kE, a.kB,
-                                                                                a.out_stride, a.kE_off, a.tw));
-    } else {
-        // strip width: the widest unless the batch is too small to give the
-        // column passes ~512 workgroups at it; then narrower strips, down to
-        // 4 columns, from n = 256 (each pass caps the request at its own
-        // widest strip)
-        constexpr int WMAX = StripF<T, LOGN>::W > StripI<T, LOGN>::W ? StripF<T, LOGN>::W
-                                                                     : StripI<T, LOGN>::W;
-        int w = WMAX;
-        while (N >= 256 && w > 4 && (long long)(N / w) * a.batch < 512) w /= 2;
-        if constexpr (WMAX >= 16) {
-            if (w == 16) return ks_launch_w<T, LOGN, 16>(a);
-        }
-        if constexpr (WMAX >= 8) {
-            if (w == 8) return ks_launch_w<T, LOGN, 8>(a);
-        }
-        return ks_launch_w<T, LOGN, 4>(a);
-    }
+template <typename T, int LOGN, bool CROP, int WREQ>
+static hipError_t cols_inv_w(const KsArgs<T>& a) {
+    constexpr int N = 1 << LOGN, W = WREQ < N / 2 ? WREQ : N / 2;
+    using S = StripI<T, LOGN, W>;
+    const int nx = CROP ? a.nx : N, ny = CROP ? a.ny : N;
+    const int strips = ((nx + 1) / 2 + S::W - 1) / S::W;
+    const int xcd = 2 * S::W * (int)sizeof(T) < 128 ? 1 : 0;
+    AMAP_LAUNCH(a.rotate ? "ks_cols_inv_noise" : "ks_cols_inv", a.stream,
+                k_ks_cols_inv<T, LOGN, CROP, W><<<dim3(strips * (a.kB ? 2 : 1), a.batch), S::NT, 0, a.stream>>>(
+                    a.C, a.kE, a.kB, a.out_stride, a.kE_off, a.tw, xcd, strips, ny, nx));
     return hipGetLastError();
+}
+
+// Which passes of a size run the three-step kernels.  Their 16 values per
+// thread leave room for four wavefronts per SIMD where the four-step kernels
+// hold 32 or 64 values and run one or two; the four-step kernels need one
+// exchange less and give the forward pass 16-column strips (128-byte row
+// segments) up to 2048 points.  Measured (us, four-step / three-step, float):
+//   row pass:      512^2: 11.6 / 9.3, x 128: 100 / 107; 1024^2 x 128: 374 / 341;
+//                  2048^2 x 32: 614 / 431
+//   inverse pass:  1024^2 x 128: 222 / 248; 2048^2 x 32: 303 / 257;
+//                  4096^2 x 8: 672 / 360
+//   forward pass:  rotating, 1024^2 x 128: 315 / 400; 2048^2 x 32: 430 / 488;
+//                  4096^2 x 8: 998 / 816
+//                  one map of 2048^2: 41 / 22; of 4096^2: 112 / 129
+//                  rotating, 1000 x 1000 in 2048^2 x 15: 154 / 131
+// Double precision from 1024 points (whose per-thread DFTs would not fit the
+// registers) has three-step kernels only.
+template <typename T, int LOGN, bool CROP>
+constexpr bool fwd3_always() { return sizeof(T) == 8 ? LOGN >= 10 : CROP && LOGN >= 11; }
+template <typename T, int LOGN>
+constexpr bool rows3() { return LOGN >= 9; }
+template <typename T, int LOGN>
+constexpr bool inv3() { return LOGN >= (sizeof(T) == 8 ? 10 : 11); }
+
+template <typename T, int LOGN, bool CROP>
+static hipError_t ks_fwd(const KsArgs<T>& a) {
+    if constexpr (fwd3_always<T, LOGN, CROP>()) {
+        return launch_ks3_fwd<T, LOGN, CROP>(a);
+    } else {
+        if constexpr (LOGN >= 11) {
+            if (a.rotate == (LOGN == 12)) return launch_ks3_fwd<T, LOGN, CROP>(a);
+        }
+        constexpr int N = 1 << LOGN, WF = StripF<T, LOGN>::W;
+        const int w = strip_width(N, CROP ? a.nx : N, a.batch, WF);
+        if constexpr (WF >= 16) {
+            if (w == 16) return cols_fwd_w<T, LOGN, CROP, 16>(a);
+        }
+        if constexpr (WF >= 8) {
+            if (w == 8) return cols_fwd_w<T, LOGN, CROP, 8>(a);
+        }
+        return cols_fwd_w<T, LOGN, CROP, 4>(a);
+    }
+}
+
+template <typename T, int LOGN, bool CROP>
+static hipError_t ks_rows(const KsArgs<T>& a) {
+    if constexpr (rows3<T, LOGN>()) {
+        return launch_ks3_rows<T, LOGN, CROP>(a);
+    } else {
+        constexpr int N = 1 << LOGN;
+        using RP = RowHalf<T, LOGN>;
+        const int nx = CROP ? a.nx : N;
+        const dim3 g((N / 2) / RP::UNITS, a.batch);
+        if (a.kB)
+            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                        k_ks_rows_half<T, LOGN, true, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+        else
+            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                        k_ks_rows_half<T, LOGN, false, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+        return hipGetLastError();
+    }
+}
+
+template <typename T, int LOGN, bool CROP>
+static hipError_t ks_inv(const KsArgs<T>& a) {
+    if constexpr (inv3<T, LOGN>()) {
+        return launch_ks3_inv<T, LOGN, CROP>(a);
+    } else {
+        constexpr int N = 1 << LOGN, WI = StripI<T, LOGN>::W;
+        const int w = strip_width(N, CROP ? (a.nx + 1) / 2 : N / 2, a.batch, WI);
+        if constexpr (WI >= 16) {
+            if (w == 16) return cols_inv_w<T, LOGN, CROP, 16>(a);
+        }
+        if constexpr (WI >= 8) {
+            if (w == 8) return cols_inv_w<T, LOGN, CROP, 8>(a);
+        }
+        return cols_inv_w<T, LOGN, CROP, 4>(a);
+    }
+}
+
+template <typename T, int LOGN, bool CROP>
+static hipError_t ks_launch_n(const KsArgs<T>& a) {
+    hipError_t e = ks_fwd<T, LOGN, CROP>(a);
+    if (e == hipSuccess) e = ks_rows<T, LOGN, CROP>(a);
+    return e == hipSuccess ? ks_inv<T, LOGN, CROP>(a) : e;
+}
+
+template <typename T, bool CROP>
+static hipError_t ks_launch_size(const KsArgs<T>& a) {
+    switch (a.logn) {
+        case 4: return ks_launch_n<T, 4, CROP>(a);
+        case 5: return ks_launch_n<T, 5, CROP>(a);
+        case 6: return ks_launch_n<T, 6, CROP>(a);
+        case 7: return ks_launch_n<T, 7, CROP>(a);
+        case 8: return ks_launch_n<T, 8, CROP>(a);
+        case 9: return ks_launch_n<T, 9, CROP>(a);
+        case 10: return ks_launch_n<T, 10, CROP>(a);
+        case 11: return ks_launch_n<T, 11, CROP>(a);
+        case 12: return ks_launch_n<T, 12, CROP>(a);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t launch_ks(const KsArgs<T>& a) {
-    switch (a.logn) {
-        case 4: return ks_launch_n<T, 4>(a);
-        case 5: return ks_launch_n<T, 5>(a);
-        case 6: return ks_launch_n<T, 6>(a);
-        case 7: return ks_launch_n<T, 7>(a);
-        case 8: return ks_launch_n<T, 8>(a);
-        case 9: return ks_launch_n<T, 9>(a);
-        case 10: return ks_launch_n<T, 10>(a);
-        case 11: return ks_launch_n<T, 11>(a);
-        case 12: return ks_launch_n<T, 12>(a);
-        default: return hipErrorInvalidValue;
-    }
+    const int N = 1 << a.logn;
+    if (a.logn < 4 || a.logn > kMaxLogN || a.batch < 1) return hipErrorInvalidValue;
+    const bool crop = a.ny > 0;
+    if (crop && (a.nx < 1 || a.ny > N || a.nx > N)) return hipErrorInvalidValue;
+    return crop && (a.ny < N || a.nx < N) ? ks_launch_size<T, true>(a) : ks_launch_size<T, false>(a);
 }
 
 template hipError_t launch_ks<float>(const KsArgs<float>&);
