@@ -106,6 +106,23 @@ inline StatLayout stat_layout(const StagePlan* p) {
     return l;
 }
 
+constexpr int kMaxScales = 12;
+constexpr int kMaxMerge = 1024;  // partials per scale the finalize kernel merges
+
+// Where a noise schedule's stages leave the statistics of one batch when they
+// are merged at the end: scale j's partial means of group g at element
+// off[j-1] + g * ns[j-1] * 2 n^2 of the batch's block of `block` elements (of
+// the accumulator type: T), its squared deviations n^2 further, in the order
+// of stat_index.  Group g of groups[j-1] holds realisations g, g + groups, ..
+// of the batch.
+struct NoiseParts {
+    bool ok = false;  // false: a stage keeps no partials
+    long long block = 0;
+    long long off[kMaxScales];
+    int groups[kMaxScales], ns[kMaxScales];
+};
+template <typename T> NoiseParts noise_parts(int logn, int J, int batch, const StagePlan* plan);
+
 template <typename T>
 struct StarletArgs {
     int logn, J, batch, done;
@@ -127,6 +144,11 @@ struct StarletArgs {
     const long long* kappa_off = nullptr;
     const long long* planes_off = nullptr;
     const StagePlan* plan = nullptr;  // tuned schedule, or null for the analytic one
+    // deferred statistics: `part` is this batch's block, laid out by parts;
+    // M and M2 are not touched.  defer without parts (one stage, timed by the
+    // tuner): the stage's partials go to the start of part.
+    const NoiseParts* parts = nullptr;
+    bool defer = false;
 };
 // Bytes of per-group partial statistics a noise batch may need.
 size_t starlet_partials_bytes(int logn, int batch);
@@ -160,6 +182,13 @@ template <typename T>
 hipError_t launch_noise_finalize(int logn, int J, int R, const double* M2,
                                  const T* planes_signal, T* sigma, T* snr, hipStream_t s,
                                  const StatLayout& layout = StatLayout());
+// The same from deferred partials: R realisations in batches of B, each
+// batch's block after the other at part; merged here in batch and group
+// order (Chan's pairwise update, double precision).
+template <typename T>
+hipError_t launch_noise_finalize_parts(int logn, int J, int R, int B, const NoiseParts& parts,
+                                       const void* part, const T* planes_signal, T* sigma, T* snr,
+                                       hipStream_t s, const StatLayout& layout);
 hipError_t launch_zero_f64(double* p, long long count, hipStream_t s);
 hipError_t launch_zero_i64(long long* p, long long count, hipStream_t s);
 

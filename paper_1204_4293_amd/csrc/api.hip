@@ -363,27 +363,45 @@ amap_status enqueue_noise(const amap_ctx* ctx, char* ws, int n, int J, const T* 
     void* part = p;                              p += align256(starlet_partials_bytes(logn, B));
     double* M = reinterpret_cast<double*>(p);    p += align256((size_t)(J - 1) * n2 * 8);
     double* M2 = reinterpret_cast<double*>(p);
+    // Statistics are merged at the end where every batch's partials fit the
+    // workspace beyond the coarse planes (tmp .. M2, which that way serve
+    // nothing else); else batch by batch into M and M2.
+    const int nbatch = (n_real + B - 1) / B;
+    const size_t room = noise_workspace_bytes(sizeof(T) == 8 ? AMAP_F64 : AMAP_F32, n, J, n_real) -
+                        (size_t)(reinterpret_cast<char*>(tmp) - ws);
+    const bool defer = (size_t)nbatch * (J - 1) * 2 * n2 * sizeof(T) <= room;
     // the schedule of a full batch serves every batch; it is tuned (if new)
-    // before the statistics are zeroed
+    // before the statistics are written
     StarletArgs<T> t;
     t.logn = logn; t.J = J; t.batch = B; t.done = 0; t.kappa = kap; t.in_stride = n2;
     t.planes = nullptr; t.planes_stride = 0; t.cbuf0 = cb0; t.cbuf1 = cb1; t.tmp = tmp;
-    t.wbuf = wb; t.M = M; t.M2 = M2; t.part = part; t.stream = s;
+    t.wbuf = wb; t.M = M; t.M2 = M2; t.part = defer ? tmp : part; t.stream = s; t.defer = defer;
     const StagePlan* plan = tuned_plan<T>(ctx, t);
+    const NoiseParts parts = defer ? noise_parts<T>(logn, J, B, plan) : NoiseParts();
+    bool deferred = parts.ok && (size_t)nbatch * parts.block * sizeof(T) <= room;
+    for (int j = 0; deferred && j < J - 1; ++j)
+        deferred = (long long)nbatch * parts.groups[j] <= kMaxMerge;
     // M and M2 need no clearing: the first batch's merges write them unread
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int bb = (n_real - r0) < B ? (n_real - r0) : B;
         AMAP_TRY(enqueue_ks<T>(ctx, logn, bb, g1, g2, 0, C, kap, nullptr, n2, true, seed,
                                (uint64_t)r0, s));
-        StarletArgs<T> a;
-        a.logn = logn; a.J = J; a.batch = bb; a.done = r0; a.kappa = kap; a.in_stride = n2;
-        a.planes = nullptr; a.planes_stride = 0; a.cbuf0 = cb0; a.cbuf1 = cb1; a.tmp = tmp;
-        a.wbuf = wb; a.M = M; a.M2 = M2; a.part = part; a.stream = s; a.plan = plan;
+        StarletArgs<T> a = t;
+        a.batch = bb; a.done = r0; a.plan = plan; a.defer = false; a.part = part;
+        if (deferred) {
+            a.parts = &parts;
+            a.part = tmp + (r0 / B) * parts.block;
+        }
         AMAP_HIP(launch_starlet<T>(a), "noise starlet kernels");
     }
-    AMAP_HIP(launch_noise_finalize<T>(logn, J, n_real, M2, planes_signal, sigma, snr, s,
-                                      stat_layout(plan)),
-             "noise finalize");
+    if (deferred)
+        AMAP_HIP(launch_noise_finalize_parts<T>(logn, J, n_real, B, parts, tmp, planes_signal, sigma, snr, s,
+                                                stat_layout(plan)),
+                 "noise finalize");
+    else
+        AMAP_HIP(launch_noise_finalize<T>(logn, J, n_real, M2, planes_signal, sigma, snr, s,
+                                          stat_layout(plan)),
+                 "noise finalize");
     return AMAP_OK;
 }
 

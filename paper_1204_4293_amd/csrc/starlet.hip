@@ -176,6 +176,21 @@ __host__ __device__ constexpr int noise_prefetch(int /*nt*/, int kv, int rb = 1)
     return kv > 1 ? 8 : (rb > 1 ? 2 : 3);
 }
 
+// G statistics of a batch to its partials (16-byte aligned), which the
+// finalize kernel reads back from memory.
+template <typename A, int G>
+__device__ __forceinline__ void store_part(A* p, const A (&v)[G]) {
+    typedef A vec __attribute__((ext_vector_type(16 / sizeof(A))));
+    constexpr int V = 16 / (int)sizeof(A);
+#pragma unroll
+    for (int i = 0; i < G; i += V) {
+        vec w;
+#pragma unroll
+        for (int c = 0; c < V; ++c) w[c] = v[i + c];
+        __builtin_nontemporal_store(w, reinterpret_cast<vec*>(p + i));
+    }
+}
+
 // Barrier that orders only LDS accesses, so global loads issued before it
 // (the next tile's prefetch) stay in flight across it.
 __device__ __forceinline__ void lds_barrier() {
@@ -599,8 +614,11 @@ __global__ void __launch_bounds__(NT) k_starlet_stage(StageArgs<T> a) {
 // realisation's tile into registers while the current one is processed.
 // Welford's running mean and sum of squared deviations of every owned pixel
 // and scale stay in registers; at the end they are merged (Chan's pairwise
-// update, double precision) into M, M2, or, with several groups, written as
-// partials that k_merge_partials folds in group order.
+// update, double precision) into M, M2, or written as partials: those of
+// every batch and group for the finalize kernel, which merges them in order
+// (8 bytes a pixel, scale and batch written and read once, where merging
+// reads and writes 32), or, where they do not all fit, those of one stage's
+// groups for k_merge_partials.
 template <typename T>
 struct NoiseStageArgs {
     int logn, j0, ns, log_tw, th;
@@ -609,7 +627,8 @@ struct NoiseStageArgs {
     int batch, groups, done;
     double* M;               // [ns][n^2] running totals of the stage's scales
     double* M2;
-    void* part;              // [groups][ns][2][n^2] partials (accumulator type) when groups > 1
+    void* part;              // [groups][ns][2][n^2] partials (accumulator type), or null: merge
+                             // into M and M2 (one group)
     float inv_tvec;          // 1 / (vectors per tile row), for index splitting
     int cout_logd = 0;       // > 0: cout in sub-grid order for d = 2^cout_logd (subgrid_index),
                              // within each image
@@ -809,7 +828,7 @@ k_starlet_noise_stage(NoiseStageArgs<T> a) {
     if (DEFER && a.cout && rounds > 0) store_coarse((rounds - 1) * RB);
     // merge into the running totals (all loads first: M and M2 do not
     // overlap), or leave partials per group
-    if (a.groups == 1) {
+    if (!a.part) {
         const double na = (double)a.done, nb = (double)count, nt = na + nb;
         const double fb = nb / nt, fab = na * nb / nt;
         double* __restrict__ Mp = a.M;
@@ -853,11 +872,8 @@ k_starlet_noise_stage(NoiseStageArgs<T> a) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 AccT* pp = static_cast<AccT*>(a.part) + ((long long)grp * NS + s) * 2 * n2;
-#pragma unroll
-                for (int c = 0; c < G; ++c) {
-                    pp[base + c] = mean[s][k][c];
-                    pp[n2 + base + c] = m2[s][k][c];
-                }
+                store_part<AccT, G>(pp + base, mean[s][k]);
+                store_part<AccT, G>(pp + n2 + base, m2[s][k]);
             }
         }
     }
@@ -879,7 +895,7 @@ struct NoiseSubArgs {
     int batch, groups, done;
     double* M;
     double* M2;
-    void* part;  // [groups][ns][2][n^2] partials when groups > 1
+    void* part;  // [groups][ns][2][n^2] partials, or null: merge into M and M2 (one group)
     int rb;      // realisations per pass (1 or 2)
 };
 
@@ -985,7 +1001,7 @@ k_starlet_noise_subgrid(NoiseSubArgs<T> a) {
         }
     }
     // merge into the running totals, or leave partials per group
-    if (a.groups == 1) {
+    if (!a.part) {
         const double na = (double)a.done, nb = (double)count, nt = na + nb;
         const double fb = nb / nt, fab = na * nb / nt;
         double* __restrict__ Mp = a.M;
@@ -1010,11 +1026,8 @@ k_starlet_noise_subgrid(NoiseSubArgs<T> a) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             AccT* pp = static_cast<AccT*>(a.part) + ((long long)grp * NS + s) * 2 * n2;
-#pragma unroll
-            for (int c = 0; c < G; ++c) {
-                pp[gown + c] = mean[s][c];
-                pp[n2 + gown + c] = m2[s][c];
-            }
+            store_part<AccT, G>(pp + gown, mean[s]);
+            store_part<AccT, G>(pp + n2 + gown, m2[s]);
         }
     }
 }
@@ -1525,48 +1538,96 @@ template bool plan_valid<double>(int, int, bool, const StagePlan&);
 template bool starlet_all_tiled<float>(int, int);
 template bool starlet_all_tiled<double>(int, int);
 
+// The stages of a transform: (j0, ns, tile), or a per-scale stage (not tiled).
+struct StageRun { int j0, ns; StageGeom g; bool tiled, sub, images; };
+
+// The stages launch_starlet runs: a schedule's (possibly a single stage, for
+// timing it), or the analytic planner's (plan null or empty).
 template <typename T>
-hipError_t launch_starlet(const StarletArgs<T>& a) {
-    const int n = 1 << a.logn;
-    const long long n2 = (long long)n * n;
-    const bool acc = a.M != nullptr;
-    // plan the stages: (j0, ns, tile) or a per-scale stage (tile.nt == 0)
-    struct Stage { int j0, ns; StageGeom g; bool tiled, sub, images; };
-    Stage plan[16];
+static hipError_t resolve_stages(int n, int J, bool acc, const StagePlan* p, StageRun* run, int* count) {
     int nstages = 0;
-    if (a.plan && a.plan->nstages > 0) {
-        // a tuned schedule (possibly a single stage, for timing it)
-        for (int k = 0; k < a.plan->nstages; ++k) {
-            const StagePlan::Stage& t = a.plan->st[k];
+    if (p && p->nstages > 0) {
+        for (int k = 0; k < p->nstages; ++k) {
+            const StagePlan::Stage& t = p->st[k];
             StageGeom g{};
             if (t.kind == kStageSubgrid) {  // a final noise stage on whole sub-grids
-                if (!acc || k + 1 != a.plan->nstages || t.j0 + t.ns != a.J || !subgrid_ok<T>(n, t.j0, a.J) ||
+                if (!acc || k + 1 != p->nstages || t.j0 + t.ns != J || !subgrid_ok<T>(n, t.j0, J) ||
                     (t.rb != 1 && t.rb != 2))
                     return hipErrorInvalidValue;
                 g.rb = t.rb;
-                plan[nstages++] = Stage{t.j0, t.ns, g, false, true, false};
+                run[nstages++] = StageRun{t.j0, t.ns, g, false, true, false};
                 continue;
             }
             if (t.kind == kStageImages) {  // noise tiles on sub-grid images
-                if (!acc || (k > 0 && a.plan->st[k - 1].kind == kStageSubgrid) ||
-                    (k + 1 < a.plan->nstages && a.plan->st[k + 1].kind == kStageTile) ||
+                if (!acc || (k > 0 && p->st[k - 1].kind == kStageSubgrid) ||
+                    (k + 1 < p->nstages && p->st[k + 1].kind == kStageTile) ||
                     !images_geom<T>(n, t.j0, t.ns, t.tw, t.th, t.rb, &g))
                     return hipErrorInvalidValue;
-                plan[nstages++] = Stage{t.j0, t.ns, g, true, false, true};
+                run[nstages++] = StageRun{t.j0, t.ns, g, true, false, true};
                 continue;
             }
             if (t.kind != kStageTile || !stage_geom_of<T>(n, t.j0, t.ns, t.tw, t.th, t.rb, acc, &g))
                 return hipErrorInvalidValue;
-            plan[nstages++] = Stage{t.j0, t.ns, g, true, false, false};
+            run[nstages++] = StageRun{t.j0, t.ns, g, true, false, false};
         }
     } else {
-        for (int j0 = 1; j0 < a.J; ) {
+        for (int j0 = 1; j0 < J; ) {
             StageGeom g{};
-            const bool tiled = pick_stage<T>(n, j0, a.J - j0, acc, &g);
+            const bool tiled = pick_stage<T>(n, j0, J - j0, acc, &g);
             const int ns = tiled ? g.ns : 1;
-            plan[nstages++] = Stage{j0, ns, g, tiled, false, false};
+            run[nstages++] = StageRun{j0, ns, g, tiled, false, false};
             j0 += ns;
         }
+    }
+    *count = nstages;
+    return hipSuccess;
+}
+
+// Workgroups per realisation group of a tiled noise stage.
+static int noise_tiles(int n, const StageRun& st) {
+    if (st.sub) return 1 << (2 * (st.j0 - 1));
+    // on sub-grid images (of side nm), the stage starts at dilation 1 there
+    const int li = st.images ? st.j0 - 1 : 0;
+    const int d0 = 1 << (st.j0 - 1 - li), nm = n >> li;
+    return ((nm / st.g.tw) * ((nm / d0) / st.g.th) * d0) << (2 * li);
+}
+
+template <typename T>
+NoiseParts noise_parts(int logn, int J, int batch, const StagePlan* plan) {
+    NoiseParts p;
+    StageRun run[16];
+    int count = 0;
+    if (resolve_stages<T>(1 << logn, J, true, plan, run, &count) != hipSuccess) return p;
+    const long long n2 = 1ll << (2 * logn);
+    for (int k = 0; k < count; ++k) {
+        if (!run[k].tiled && !run[k].sub) return p;  // per-scale stages keep no partials
+        const int groups = noise_groups(noise_tiles(1 << logn, run[k]), batch);
+        for (int s = 0; s < run[k].ns; ++s) {
+            const int j = run[k].j0 + s;
+            if (j >= J || j > kMaxScales) return p;
+            p.off[j - 1] = p.block + s * 2 * n2;
+            p.groups[j - 1] = groups;
+            p.ns[j - 1] = run[k].ns;
+        }
+        p.block += (long long)groups * run[k].ns * 2 * n2;
+    }
+    p.ok = true;
+    return p;
+}
+template NoiseParts noise_parts<float>(int, int, int, const StagePlan*);
+template NoiseParts noise_parts<double>(int, int, int, const StagePlan*);
+
+template <typename T>
+hipError_t launch_starlet(const StarletArgs<T>& a) {
+    using AccT = typename std::conditional<sizeof(T) == 8, double, float>::type;
+    const int n = 1 << a.logn;
+    const long long n2 = (long long)n * n;
+    const bool acc = a.M != nullptr;
+    StageRun plan[16];
+    int nstages = 0;
+    {
+        const hipError_t e = resolve_stages<T>(n, a.J, acc, a.plan, plan, &nstages);
+        if (e != hipSuccess) return e;
     }
     if (a.planes_off) {
         // grouped maps: c ping-pongs between cbuf0 and cbuf1; the last stage
@@ -1574,7 +1635,7 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
         if (acc || !a.cbuf0 || !a.cbuf1) return hipErrorInvalidValue;
         const T* cur = a.kappa_off ? nullptr : a.kappa;  // keeps the first stage's output off its input
         for (int gi = 0; gi < nstages; ++gi) {
-            const Stage& st = plan[gi];
+            const StageRun& st = plan[gi];
             if (!st.tiled) return hipErrorNotSupported;
             const bool last = st.j0 + st.ns == a.J;
             int lt = 0;
@@ -1591,13 +1652,38 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
         }
         return hipGetLastError();
     }
+    // Where a noise stage leaves its statistics: with deferred partials in
+    // its place of the batch's block (a single stage timed by the tuner: at
+    // the block's start), else merged into M and M2, by itself (one group) or
+    // through partials of its groups.
+    auto stage_partials = [&](const StageRun& st, int tiles, int* groups, void** part) {
+        if (a.parts || a.defer) {
+            *groups = a.parts ? a.parts->groups[st.j0 - 1] : noise_groups(tiles, a.batch);
+            *part = static_cast<AccT*>(a.part) + (a.parts ? a.parts->off[st.j0 - 1] : 0);
+            return hipSuccess;
+        }
+        *groups = noise_groups(tiles, a.batch);
+        *part = *groups > 1 ? a.part : nullptr;
+        return *groups > 1 && (size_t)*groups * st.ns * 2 * (size_t)n2 * sizeof(AccT) >
+                                  starlet_partials_bytes(a.logn, a.batch)
+                   ? hipErrorInvalidConfiguration
+                   : hipSuccess;
+    };
+    auto merge_groups = [&](const StageRun& st, int groups, const void* part) {
+        if (a.parts || a.defer || groups == 1) return hipSuccess;
+        AMAP_LAUNCH("merge_partials", a.stream,
+                    k_merge_partials<AccT><<<(unsigned)((n2 + 255) / 256), 256, 0, a.stream>>>(
+                        static_cast<const AccT*>(part), groups, st.ns, a.batch, a.done, n2,
+                        a.M + (long long)(st.j0 - 1) * n2, a.M2 + (long long)(st.j0 - 1) * n2));
+        return hipGetLastError();
+    };
     T* final_c = acc ? nullptr : a.planes + (long long)(a.J - 1) * n2;
     const long long final_stride = a.planes_stride;
     const T* cur = a.kappa;
     long long cur_stride = a.in_stride;
     if (acc && a.in_stride != n2) return hipErrorInvalidValue;  // realisations are packed
     for (int gi = 0; gi < nstages; ++gi) {
-        const Stage& st = plan[gi];
+        const StageRun& st = plan[gi];
         const bool last = st.j0 + st.ns == a.J;
         T* dst;
         long long dst_stride;
@@ -1618,44 +1704,24 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
         while ((1 << lt) < st.g.tw) ++lt;
         if (st.sub) {  // acc only, the last stage: c and the statistics in sub-grid order
             // (after a stage on sub-grid images, their sub-grids image by image)
-            const int d0 = 1 << (st.j0 - 1);
-            const int tiles = d0 * d0;
-            int logm = 0;
-            while ((1 << logm) < n / d0) ++logm;
+            const int tiles = noise_tiles(n, st);
             NoiseSubArgs<T> s;
             s.logn = a.logn; s.j0 = st.j0; s.src = cur; s.batch = a.batch; s.rb = st.g.rb;
-            s.groups = noise_groups(tiles, a.batch); s.done = a.done;
+            s.done = a.done;
             s.M = a.M + (long long)(st.j0 - 1) * n2; s.M2 = a.M2 + (long long)(st.j0 - 1) * n2;
-            s.part = a.part;
-            {
-                using AccT = typename std::conditional<sizeof(T) == 8, double, float>::type;
-                if (s.groups > 1 && (size_t)s.groups * st.ns * 2 * (size_t)n2 * sizeof(AccT) >
-                                        starlet_partials_bytes(a.logn, a.batch))
-                    return hipErrorInvalidConfiguration;
-            }
-            e = launch_subgrid<T>(s, st.ns, logm, tiles, a.stream);
-            if (e == hipSuccess && s.groups > 1) {
-                using AccT = typename std::conditional<sizeof(T) == 8, double, float>::type;
-                AMAP_LAUNCH("merge_partials", a.stream,
-                            k_merge_partials<AccT><<<(unsigned)((n2 + 255) / 256), 256, 0, a.stream>>>(
-                                static_cast<const AccT*>(a.part), s.groups, st.ns, a.batch, a.done,
-                                n2, s.M, s.M2));
-                e = hipGetLastError();
-            }
+            e = stage_partials(st, tiles, &s.groups, &s.part);
+            if (e == hipSuccess) e = launch_subgrid<T>(s, st.ns, a.logn - (st.j0 - 1), tiles, a.stream);
+            if (e == hipSuccess) e = merge_groups(st, s.groups, s.part);
             if (e != hipSuccess) return e;
             continue;
         }
         if (st.tiled && acc) {
-            // on sub-grid images (of side nm), the stage starts at dilation 1 there
-            const int li = st.images ? st.j0 - 1 : 0;
-            const int d0 = 1 << (st.j0 - 1 - li), nm = n >> li;
-            const int tiles = ((nm / st.g.tw) * ((nm / d0) / st.g.th) * d0) << (2 * li);
+            const int li = st.images ? st.j0 - 1 : 0, d0 = 1 << (st.j0 - 1 - li);
+            const int tiles = noise_tiles(n, st);
             NoiseStageArgs<T> s;
             s.logn = a.logn; s.j0 = st.j0; s.ns = st.ns; s.log_tw = lt; s.th = st.g.th;
-            s.src = cur; s.cout = dst; s.batch = a.batch;
-            s.groups = noise_groups(tiles, a.batch); s.done = a.done;
+            s.src = cur; s.cout = dst; s.batch = a.batch; s.done = a.done;
             s.M = a.M + (long long)(st.j0 - 1) * n2; s.M2 = a.M2 + (long long)(st.j0 - 1) * n2;
-            s.part = a.part;
             s.inv_tvec = 1.0f / (float)((st.g.tw + 2 * stage_hx(d0, st.ns, Vec<T>::G)) / Vec<T>::G);
             // a following sub-grid or sub-grid image stage reads c in its
             // sub-grid order (within each image of this one)
@@ -1663,21 +1729,9 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
             s.cout_logd = (gi + 1 < nstages && (plan[gi + 1].sub || plan[gi + 1].images))
                               ? plan[gi + 1].j0 - 1 - li
                               : (a.plan && nstages == 1 && dst ? a.plan->cout_logd : 0);
-            {
-                using AccT = typename std::conditional<sizeof(T) == 8, double, float>::type;
-                if (s.groups > 1 && (size_t)s.groups * st.ns * 2 * (size_t)n2 * sizeof(AccT) >
-                                        starlet_partials_bytes(a.logn, a.batch))
-                    return hipErrorInvalidConfiguration;
-            }
-            e = launch_noise_stage<T>(s, st.g, tiles, a.stream);
-            if (e == hipSuccess && s.groups > 1) {
-                using AccT = typename std::conditional<sizeof(T) == 8, double, float>::type;
-                AMAP_LAUNCH("merge_partials", a.stream,
-                            k_merge_partials<AccT><<<(unsigned)((n2 + 255) / 256), 256, 0, a.stream>>>(
-                                static_cast<const AccT*>(a.part), s.groups, st.ns, a.batch, a.done,
-                                n2, s.M, s.M2));
-                e = hipGetLastError();
-            }
+            e = stage_partials(st, tiles, &s.groups, &s.part);
+            if (e == hipSuccess) e = launch_noise_stage<T>(s, st.g, tiles, a.stream);
+            if (e == hipSuccess) e = merge_groups(st, s.groups, s.part);
             if (e != hipSuccess) return e;
             cur = dst;
             cur_stride = dst_stride;

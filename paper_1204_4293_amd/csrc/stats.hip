@@ -40,6 +40,126 @@ k_noise_finalize(const double* __restrict__ M2, int R, int J, int logn, StatLayo
     }
 }
 
+// sigma and S/N of scale blockIdx.y + 1 from the partials of every batch and
+// group, merged in order.  A block takes 2^logcp pixels (a row segment, or
+// whole rows) and walks them in the order their statistics lie in memory: on
+// sub-grids of d, the pixels of one residue mod d after the other, so that a
+// wavefront reads runs and not a line per lane; sigma goes through LDS (a
+// row padded by one per d pixels, against bank conflicts) into row order for
+// the stores.  The merge weights are worked out once per block.  Bound by its
+// reads (8 bytes a partial): 4096^2, J = 9, four batches, 1.3 ms; one lane
+// per pixel in row order took 3.2.
+template <typename T, typename A>
+__global__ void __launch_bounds__(256)
+k_noise_finalize_parts(const A* __restrict__ part, NoiseParts np, int R, int B, int logn, int logcp,
+                       StatLayout lay, const T* __restrict__ planes_signal, T* __restrict__ sigma,
+                       T* __restrict__ snr) {
+    extern __shared__ __align__(16) unsigned char fin_smem[];
+    const long long n2 = 1ll << (2 * logn);
+    const int j = blockIdx.y;
+    const int G = np.groups[j];
+    const int total = (R + B - 1) / B * G;  // partials: batch by batch, group by group
+    double* f = reinterpret_cast<double*>(fin_smem);  // nb / nt of each
+    double* h = f + total;                            // na nb / nt
+    T* sg = reinterpret_cast<T*>(h + total);
+    for (int k = threadIdx.x; k < total; k += 256) {
+        const int b = k / G, g = k - b * G;
+        const int bb = R - b * B < B ? R - b * B : B;
+        const int q = bb / G, r = bb - q * G;  // group g holds q (+ 1 if g < r) realisations
+        const double nb = (double)(q + (g < r ? 1 : 0)), na = (double)(b * B + g * q + (g < r ? g : r));
+        f[k] = nb / (na + nb);  // the first group of a batch is never empty
+        h[k] = na * f[k];
+    }
+    __syncthreads();
+    int ld = 0;  // log2 of the scale's sub-grid stride
+    for (int k = 0; k < lay.count && lay.j0[k] <= j + 1; ++k) ld = lay.j0[k] - 1;
+    const int logwx = logn < logcp ? logn : logcp, logper = logwx - ld;
+    const int wx = 1 << logwx, per = 1 << logper, pitch = wx + per;
+    const long long px0 = (long long)blockIdx.x << logcp;
+    const A* base = part + np.off[j];
+    const long long gs = (long long)np.ns[j] * 2 * n2;  // elements per group
+    // pixel e of the block in memory order: where its partials lie and where its sigma goes in LDS
+    const auto locate = [&](int e, int& at) {
+        const int row = e >> logwx, i = e & (wx - 1);
+        const int xx = i & (per - 1), x = (i >> logper) + (xx << ld);
+        at = row * pitch + x + xx;
+        return base + stat_index(px0 + ((long long)row << logwx) + x, logn, j + 1, lay);
+    };
+    const auto finish = [&](double m2, int at) {
+        double var = m2 / (double)(R - 1);
+        var = var > 0.0 ? var : 0.0;
+        sg[at] = (T)sqrt(var);
+    };
+    const int npx = 1 << logcp;
+    if (total == 1) {
+        constexpr int U = 4;  // pixels in flight
+        for (int e0 = threadIdx.x; e0 < npx; e0 += U * 256) {
+            A v[U];
+            int at[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (e0 + u * 256 < npx) v[u] = locate(e0 + u * 256, at[u])[n2];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (e0 + u * 256 < npx) finish((double)v[u], at[u]);
+        }
+    } else {
+        for (int e0 = threadIdx.x; e0 < npx; e0 += 2 * 256) {
+            // two pixels, four partials of each in flight (npx is 256 or even)
+            const bool two = e0 + 256 < npx;
+            int at[2];
+            const A* p[2];
+            p[0] = locate(e0, at[0]);
+            p[1] = locate(two ? e0 + 256 : e0, at[1]);
+            const A* q[2] = {p[0], p[1]};  // partial k, and its batch's first
+            double mean[2] = {0.0, 0.0}, m2[2] = {0.0, 0.0};
+            int g = 0;
+            for (int k0 = 0; k0 < total; k0 += 4) {
+                A mb[4][2], qb[4][2];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        if (k0 + u < total) {
+                            mb[u][c] = q[c][0];
+                            qb[u][c] = q[c][n2];
+                        }
+                        q[c] += gs;
+                    }
+                    if (++g == G) {
+                        g = 0;
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            p[c] += np.block;
+                            q[c] = p[c];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (k0 + u >= total) continue;
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const double d = (double)mb[u][c] - mean[c];
+                        mean[c] += d * f[k0 + u];
+                        m2[c] += (double)qb[u][c] + d * d * h[k0 + u];
+                    }
+                }
+            }
+            finish(m2[0], at[0]);
+            if (two) finish(m2[1], at[1]);
+        }
+    }
+    __syncthreads();
+    const long long o = (long long)j * n2 + px0;
+    for (int e = threadIdx.x; e < (1 << logcp); e += 256) {
+        const int row = e >> logwx, x = e & (wx - 1);
+        const T v = sg[row * pitch + x + (x >> ld)];
+        sigma[o + e] = v;
+        if (snr) snr[o + e] = v > (T)0 ? planes_signal[o + e] / v : (T)0;
+    }
+}
+
 __global__ void k_zero_f64(double* p, long long count) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i < count) p[i] = 0.0;
@@ -322,6 +442,31 @@ hipError_t launch_noise_finalize(int logn, int J, int R, const double* M2,
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_noise_finalize_parts(int logn, int J, int R, int B, const NoiseParts& parts,
+                                       const void* part, const T* planes_signal, T* sigma, T* snr,
+                                       hipStream_t s, const StatLayout& layout) {
+    if (!parts.ok || J - 1 > kMaxScales || B < 1 || layout.count < 0 || layout.count > 16)
+        return hipErrorInvalidValue;
+    // pixels per block: 2048 (8 per thread), fewer while that leaves the chip
+    // short of blocks, 256 at least; a segment holds whole strides of the
+    // sub-grids
+    int logcp = 11;
+    while (logcp > 8 && ((J - 1) << (2 * logn)) >> logcp < 8192) --logcp;
+    int ld = 0, most = 0;
+    for (int k = 0; k < layout.count; ++k) ld = layout.j0[k] - 1;
+    if (logcp < ld) logcp = ld;
+    if (logcp > 2 * logn || ld > logn) return hipErrorInvalidValue;
+    for (int j = 0; j < J - 1; ++j) most = parts.groups[j] > most ? parts.groups[j] : most;
+    const long long total = (long long)((R + B - 1) / B) * most;
+    if (total < 1 || total > kMaxMerge) return hipErrorInvalidValue;
+    const size_t lds = (size_t)total * 2 * sizeof(double) + (2ull << logcp) * sizeof(T);
+    AMAP_LAUNCH("noise_finalize", s,
+                k_noise_finalize_parts<T, T><<<dim3(1u << (2 * logn - logcp), J - 1), 256, lds, s>>>(
+                    static_cast<const T*>(part), parts, R, B, logn, logcp, layout, planes_signal, sigma, snr));
+    return hipGetLastError();
+}
+
 hipError_t launch_zero_f64(double* p, long long count, hipStream_t s) {
     if (count > 0) AMAP_LAUNCH("zero", s, k_zero_f64<<<blocks_for(count), 256, 0, s>>>(p, count));
     return hipGetLastError();
@@ -384,6 +529,12 @@ template hipError_t launch_noise_finalize<float>(int, int, int, const double*, c
                                                  float*, hipStream_t, const StatLayout&);
 template hipError_t launch_noise_finalize<double>(int, int, int, const double*, const double*,
                                                   double*, double*, hipStream_t, const StatLayout&);
+template hipError_t launch_noise_finalize_parts<float>(int, int, int, int, const NoiseParts&, const void*,
+                                                       const float*, float*, float*, hipStream_t,
+                                                       const StatLayout&);
+template hipError_t launch_noise_finalize_parts<double>(int, int, int, int, const NoiseParts&, const void*,
+                                                        const double*, double*, double*, hipStream_t,
+                                                        const StatLayout&);
 template hipError_t launch_count_peaks<float>(int, int, const float*, double, long long*, hipStream_t);
 template hipError_t launch_count_peaks<double>(int, int, const double*, double, long long*, hipStream_t);
 template hipError_t launch_peak_hist<float>(int, int, const float*, int, double, double, int, long long*,
