@@ -215,14 +215,18 @@ template <typename T>
 hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T* planes, T* tmp,
                              int maps, long long image_stride, long long planes_stride, hipStream_t s);
 
-// Welford's update of the running mean M and squared deviations M2 (double,
-// `count` elements) with the values of realisations r0 .. r0+nb-1 in order,
-// w_stride apart (realisation 0 writes them unread);
-// sigma = sqrt(M2/(R-1)) and, if snr is not null, snr = w_signal / sigma (0
-// where sigma = 0).
+// Scales of a J-plane transform that run as tiles (the rest need scratch).
+int bc_tile_scales(int J, size_t elem);
+// Noise statistics of nb realisations' ny x nx kappa maps (realisations r0 ..
+// r0+nb-1 of R, packed, overwritten): every detail plane's running mean and
+// squared deviations continue in M and M2 ([J-1][ny][nx], double; Welford's
+// update in order, realisation 0 writes them unread) and, with the last
+// realisation, end as sigma = sqrt(M2/(R-1)) and, if snr is not null,
+// snr = w_signal / sigma (0 where sigma = 0).  Scratch of nb*ny*nx each: tmp,
+// and, if not every scale runs as tiles, row and wpl.
 template <typename T>
-hipError_t launch_welford_bc(const T* w, long long w_stride, int nb, double* M, double* M2,
-                             long long count, int r0, hipStream_t s);
+hipError_t launch_noise_bc(int ny, int nx, int J, int mode, T* kappa, T* tmp, T* row, T* wpl, int nb, int r0,
+                           int R, double* M, double* M2, const T* w_signal, T* sigma, T* snr, hipStream_t s);
 // Peaks above thr of nplanes ny x nx planes under an edge rule (counts:
 // nplanes long long, overwritten); with a mask (NULL: none) only peaks whose
 // pixel and in-field neighbours are observed.
@@ -235,8 +239,4 @@ hipError_t launch_count_peaks_bc(int ny, int nx, int nplanes, int mode, const T*
 template <typename T>
 hipError_t launch_mask_shear(long long count, const T* g1, const T* g2, const unsigned char* mask,
                              T* o1, T* o2, hipStream_t s);
-template <typename T>
-hipError_t launch_sigma_snr_bc(const double* M2, int R, const T* w_signal, T* sigma, T* snr,
-                               long long count, hipStream_t s);
-
 }  // namespace amap

@@ -907,20 +907,24 @@ amap_status amap_mask_shear(amap_ctx_t c, amap_dtype dt, int ny, int nx, const u
 
 }  // extern "C"
 
+// Field-sized buffers per realisation of the bounded noise path: kappa and
+// the coarse plane beside it, and, for dilations beyond the tiles, a row pass
+// and a detail plane.
+static size_t bounded_noise_fields(int J, size_t esz) { return bc_tile_scales(J, esz) == J - 1 ? 2 : 4; }
 // Realisations per launch of the bounded noise path: as many as fit about
-// 1 GiB of workspace (a P^2 spectrum, and a field-sized kappa, scratch and
-// planes per realisation), 1 .. 32.
+// 1 GiB of workspace (a P^2 spectrum and the field-sized buffers each), 1 ..
+// 32, evened out over the batches that takes.
 static int bounded_noise_batch(int ny, int nx, int P, int J, size_t esz, int n_real) {
-    const size_t per = 2 * (size_t)P * P * esz + (size_t)(2 + J) * ny * nx * esz;
+    const size_t per = 2 * (size_t)P * P * esz + bounded_noise_fields(J, esz) * ny * nx * esz;
     size_t b = ((size_t)1 << 30) / per;
     if (b < 1) b = 1;
     if (b > 32) b = 32;
-    if (b > (size_t)n_real) b = (size_t)n_real;
-    return (int)b;
+    const size_t batches = ((size_t)n_real + b - 1) / b;
+    return (int)(((size_t)n_real + batches - 1) / batches);
 }
 static size_t bounded_noise_bytes(int ny, int nx, int P, int J, size_t esz, int B) {
     const size_t pp = (size_t)P * P * esz * B, ff = (size_t)ny * nx * esz * B;
-    return align256(2 * pp) + 2 * align256(ff) + align256(ff * J) +
+    return align256(2 * pp) + bounded_noise_fields(J, esz) * align256(ff) +
            2 * align256((size_t)(J - 1) * ny * nx * 8);
 }
 
@@ -930,24 +934,21 @@ static amap_status enqueue_noise_bc(const amap_ctx* c, char* w, int ny, int nx, 
                                     const T* planes_signal, T* sigma, T* snr, hipStream_t s) {
     const int B = bounded_noise_batch(ny, nx, P, J, sizeof(T), n_real);
     const long long pn = (long long)P * P, fn = (long long)ny * nx;
-    const size_t pp = (size_t)pn * sizeof(T) * B, ff = (size_t)fn * sizeof(T) * B;
-    const long long cnt = (long long)(J - 1) * fn;
+    const size_t ff = align256((size_t)fn * sizeof(T) * B);
     char* q = w;
-    cpx<T>* C = reinterpret_cast<cpx<T>*>(q);  q += align256(2 * pp);
-    T* kap = reinterpret_cast<T*>(q);          q += align256(ff);
-    T* tmp = reinterpret_cast<T*>(q);          q += align256(ff);
-    T* pl = reinterpret_cast<T*>(q);           q += align256(ff * J);
-    double* M = reinterpret_cast<double*>(q);  q += align256((size_t)cnt * 8);
+    cpx<T>* C = reinterpret_cast<cpx<T>*>(q);  q += align256(2 * (size_t)pn * sizeof(T) * B);
+    T* field[4] = {nullptr, nullptr, nullptr, nullptr};
+    for (size_t k = 0; k < bounded_noise_fields(J, sizeof(T)); ++k, q += ff) field[k] = reinterpret_cast<T*>(q);
+    double* M = reinterpret_cast<double*>(q);  q += align256((size_t)(J - 1) * fn * 8);
     double* M2 = reinterpret_cast<double*>(q);
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int nb = n_real - r0 < B ? n_real - r0 : B;
-        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, g1, g2, 0, C, kap, nullptr, fn, true, seed, (uint64_t)r0, s,
+        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, g1, g2, 0, C, field[0], nullptr, fn, true, seed, (uint64_t)r0, s,
                                ny, nx));
-        AMAP_HIP(launch_starlet_bc<T>(ny, nx, J, boundary, kap, pl, tmp, nb, fn, (long long)J * fn, s),
-                 "bounded starlet kernels");
-        AMAP_HIP(launch_welford_bc<T>(pl, (long long)J * fn, nb, M, M2, cnt, r0, s), "statistics kernel");
+        AMAP_HIP(launch_noise_bc<T>(ny, nx, J, boundary, field[0], field[1], field[2], field[3], nb, r0, n_real,
+                                    M, M2, planes_signal, sigma, snr, s),
+                 "bounded noise kernels");
     }
-    AMAP_HIP(launch_sigma_snr_bc<T>(M2, n_real, planes_signal, sigma, snr, cnt, s), "sigma kernel");
     return AMAP_OK;
 }
 

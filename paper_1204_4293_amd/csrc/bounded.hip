@@ -63,18 +63,18 @@ k_bc_row(const T* __restrict__ c, T* __restrict__ r, int nx, int d, int mode, lo
 
 // c_next[y][x] = sum_t h_t r[y + (t-2) d][x], w = c_prev - c_next.  c_prev
 // and c_next may be the same array: each thread reads and writes only its
-// own pixel of them.  grid (ceil(nx/256), ny, maps); map z's w and c_next
-// at + z pl_stride
+// own pixel of them.  grid (ceil(nx/256), ny, maps); map z's w
+// at + z w_stride, its c_next at + z cn_stride
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_bc_col(const T* __restrict__ r, const T* c_prev, T* __restrict__ w, T* c_next, int ny, int nx,
-         int d, int mode, long long r_stride, long long cp_stride, long long pl_stride) {
+         int d, int mode, long long r_stride, long long cp_stride, long long w_stride, long long cn_stride) {
     const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
     if (x >= nx) return;
     r += blockIdx.z * r_stride;
     c_prev += blockIdx.z * cp_stride;
-    w += blockIdx.z * pl_stride;
-    c_next += blockIdx.z * pl_stride;
+    w += blockIdx.z * w_stride;
+    c_next += blockIdx.z * cn_stride;
     T v[5];
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
@@ -88,59 +88,156 @@ k_bc_col(const T* __restrict__ r, const T* c_prev, T* __restrict__ w, T* c_next,
     c_next[o] = cn;
 }
 
-// One smoothing step at dilation d as a tile: kBcTW consecutive columns by
-// kBcTH rows of one residue class ry (mod d) of the rows, y = ry + d (M0 + m).
-// Taps of the column pass then stay in the class (the edge rule maps each
-// tap row on its own, so the tile simply loads the mapped rows), and the
-// tile stages kBcTH + 4 rows of kBcTW + 4d columns of c_{j-1} once: the row
-// pass runs in LDS on all of them, the column pass on the kBcTH middle rows,
-// and w_j = c_{j-1} - c_j and c_j are written (c_j to a buffer apart from
-// c_{j-1}, whose halo other tiles still read).  grid (column tiles,
-// d * row-tile count, maps); dynamic LDS (kBcTH + 4)(kBcTW + 4d + kBcTW) T,
-// under 64 KiB up to dilation bc_max_d.
-constexpr int kBcTW = 64, kBcTH = 16;
+// One smoothing step at dilation d as a tile: 64 columns by kBcTH rows of one
+// residue class ry (mod d) of the rows, y = ry + d (M0 + m).  Taps of the
+// column pass then stay in the class (the edge rule maps each tap row on its
+// own, so the tile simply loads the mapped rows), and the tile stages
+// kBcTH + 4 rows of 64 + 4d columns of c_{j-1} once: the row pass runs in LDS
+// on all of them, the column pass on the kBcTH middle rows, and c_j goes to a
+// buffer apart from c_{j-1}, whose halo other tiles still read.  A lane
+// keeps one column: it stages column chunks of 64, so the edge rule is worked
+// out once per chunk and row (uniform), not per value, and its wavefront owns
+// kBcTH / 4 consecutive output rows, a sliding window down the column.
+//
+// NOISE: the tile takes nb realisations in turn, the next one's values on
+// their way (in registers) while the current one is filtered, and keeps
+// Welford's mean and squared deviations of its pixels in registers (double):
+// w_j goes nowhere.  They continue from M and M2 unless r0 = 0 and end there,
+// or, with the last realisation (r0 + nb = R), as sigma and S/N.  Else
+// (signal): blockIdx.z is the map, w_j = c_{j-1} - c_j is stored.
+//
+// Bound by memory traffic (8 bytes a pixel, scale and realisation, and the
+// halos through L2).  16 realisations of a 1000 x 1000 float field, one
+// scale: 57 us (d <= 16) to 75 (d = 32), where storing w_j and a pass for the
+// statistics took 109; one map: 6.5 to 9.5 us, 9.5 with the edge rule worked
+// out per value.
+// grid (column tiles, d * row tiles, maps or 1); dynamic LDS
+// (kBcTH + 4)(64 + 4d + 64) T, under 64 KiB up to dilation bc_max_d.  KC:
+// column chunks of a staged row.
+constexpr int kBcTH = 16;
 template <typename T>
 constexpr int bc_max_d() { return sizeof(T) == 4 ? 128 : 64; }
+
 template <typename T>
+struct BcArgs {
+    const T* c_prev;
+    T* c_next;  // null (NOISE): the last scale
+    T* w;       // signal: w_j
+    int ny, nx, d, mode;
+    long long cp_stride, cn_stride, w_stride;  // per map or realisation
+    // NOISE
+    int nb, r0, R;
+    double *M, *M2;
+    const T* w_signal;
+    T *sigma, *snr;
+};
+
+template <typename T, bool NOISE, int KC>
 __global__ void __launch_bounds__(256)
-k_bc_scale_tile(const T* __restrict__ c_prev, T* __restrict__ w, T* __restrict__ c_next, int ny,
-                int nx, int d, int mode, long long cp_stride, long long cn_stride, long long w_stride) {
+k_bc_scale(BcArgs<T> a) {
+    constexpr int ROWS = kBcTH + 4, RPW = ROWS / 4, OPW = kBcTH / 4;  // staged and output rows per wavefront
     extern __shared__ unsigned char lds_raw[];
-    T* reg = reinterpret_cast<T*>(lds_raw);            // [kBcTH + 4][RW]
-    const int RW = kBcTW + 4 * d;
-    T* rr = reg + (kBcTH + 4) * RW;                    // [kBcTH + 4][kBcTW]
-    const int x0 = blockIdx.x * kBcTW;
+    T* reg = reinterpret_cast<T*>(lds_raw);  // [ROWS][RW]
+    const int d = a.d, RW = 64 + 4 * d;
+    T* rr = reg + ROWS * RW;                 // [ROWS][64]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int x0 = blockIdx.x * 64;
     const int ry = blockIdx.y % d, M0 = (blockIdx.y / d) * kBcTH;
-    c_prev += blockIdx.z * cp_stride;
-    c_next += blockIdx.z * cn_stride;
-    w += blockIdx.z * w_stride;
-    // stage: region row m is c_{j-1} row bc(ry + d (M0 + m - 2)), region
-    // column i is column bc(x0 - 2d + i)
-    for (int e = threadIdx.x; e < (kBcTH + 4) * RW; e += 256) {
-        const int m = e / RW, i = e - m * RW;
-        const int yy = bc_index(ry + d * (M0 + m - 2), ny, mode);
-        const int xx = bc_index(x0 - 2 * d + i, nx, mode);
-        reg[e] = (yy < 0 || xx < 0) ? (T)0 : c_prev[(long long)yy * nx + xx];
+    const long long plane = (long long)a.ny * a.nx;
+    // this lane's staged columns and its wavefront's staged rows (-1: 0)
+    int col[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+        const int i = lane + 64 * k;
+        col[k] = i < RW ? bc_index(x0 - 2 * d + i, a.nx, a.mode) : -1;
     }
-    __syncthreads();
-    // row pass on every staged row
-    for (int e = threadIdx.x; e < (kBcTH + 4) * kBcTW; e += 256) {
-        const int m = e / kBcTW, i = e - m * kBcTW;
-        const T* g = reg + m * RW + i;
-        rr[e] = b3(g[0], g[d], g[2 * d], g[3 * d], g[4 * d]);
+    int row[RPW];
+#pragma unroll
+    for (int q = 0; q < RPW; ++q) row[q] = bc_index(ry + d * (M0 + wave + 4 * q - 2), a.ny, a.mode);
+    // owned pixels: column x of OPW rows
+    const int x = x0 + lane;
+    const auto out_row = [&](int k) { return ry + d * (M0 + OPW * wave + k); };
+    T v[RPW][KC];
+    const auto fetch = [&](const T* src) {
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            const T* p = src + (long long)(row[q] < 0 ? 0 : row[q]) * a.nx;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+                const T t = p[col[k] < 0 ? 0 : col[k]];
+                v[q][k] = row[q] < 0 || col[k] < 0 ? (T)0 : t;
+            }
+        }
+    };
+    double mean[OPW], m2[OPW];
+    if constexpr (NOISE) {
+#pragma unroll
+        for (int k = 0; k < OPW; ++k) {
+            const int y = out_row(k);
+            const bool in = a.r0 > 0 && y < a.ny && x < a.nx;
+            mean[k] = in ? a.M[(long long)y * a.nx + x] : 0.0;
+            m2[k] = in ? a.M2[(long long)y * a.nx + x] : 0.0;
+        }
     }
-    __syncthreads();
-    // column pass on the middle rows
-    for (int e = threadIdx.x; e < kBcTH * kBcTW; e += 256) {
-        const int m = e / kBcTW, i = e - m * kBcTW;
-        const int y = ry + d * (M0 + m), x = x0 + i;
-        if (y >= ny || x >= nx) continue;
-        const T* g = rr + m * kBcTW + i;
-        const T cn = b3(g[0], g[kBcTW], g[2 * kBcTW], g[3 * kBcTW], g[4 * kBcTW]);
-        const T cp = reg[(m + 2) * RW + 2 * d + i];
-        const long long o = (long long)y * nx + x;
-        w[o] = cp - cn;
-        c_next[o] = cn;
+    const int maps = NOISE ? a.nb : 1;
+    const long long first = NOISE ? 0 : blockIdx.z;
+    fetch(a.c_prev + first * a.cp_stride);
+    for (int b = 0; b < maps; ++b) {
+        const long long map = first + b;
+        __syncthreads();  // the previous map's reads of the tile are done
+#pragma unroll
+        for (int q = 0; q < RPW; ++q)
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+                if (lane + 64 * k < RW) reg[(wave + 4 * q) * RW + lane + 64 * k] = v[q][k];
+        if (NOISE && b + 1 < maps) fetch(a.c_prev + (map + 1) * a.cp_stride);
+        __syncthreads();
+        // row pass on every staged row
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            const T* g = reg + (wave + 4 * q) * RW + lane;
+            rr[(wave + 4 * q) * 64 + lane] = b3(g[0], g[d], g[2 * d], g[3 * d], g[4 * d]);
+        }
+        __syncthreads();
+        // column pass on this wavefront's output rows
+        T win[OPW + 4];
+#pragma unroll
+        for (int k = 0; k < OPW + 4; ++k) win[k] = rr[(OPW * wave + k) * 64 + lane];
+        const double inv = NOISE ? 1.0 / (double)(a.r0 + b + 1) : 0.0;
+#pragma unroll
+        for (int k = 0; k < OPW; ++k) {
+            const int y = out_row(k);
+            const T cn = b3(win[k], win[k + 1], win[k + 2], win[k + 3], win[k + 4]);
+            const T wv = reg[(OPW * wave + k + 2) * RW + 2 * d + lane] - cn;
+            const bool in = y < a.ny && x < a.nx;
+            const long long o = (long long)y * a.nx + x;
+            if (in && (!NOISE || a.c_next)) a.c_next[map * a.cn_stride + o] = cn;
+            if constexpr (NOISE) {
+                const double dl = (double)wv - mean[k];
+                mean[k] = fma(dl, inv, mean[k]);
+                m2[k] = fma(dl, (double)wv - mean[k], m2[k]);
+            } else {
+                if (in) a.w[map * a.w_stride + o] = wv;
+            }
+        }
+    }
+    if constexpr (NOISE) {
+        const bool last = a.r0 + a.nb == a.R;
+#pragma unroll
+        for (int k = 0; k < OPW; ++k) {
+            const int y = out_row(k);
+            if (y >= a.ny || x >= a.nx) continue;
+            const long long o = (long long)y * a.nx + x;
+            if (last) {
+                const double sg = sqrt(m2[k] / (double)(a.R - 1));
+                a.sigma[o] = (T)sg;
+                if (a.snr) a.snr[o] = sg > 0.0 ? (T)((double)a.w_signal[o] / sg) : (T)0;
+            } else {
+                a.M[o] = mean[k];
+                a.M2[o] = m2[k];
+            }
+        }
     }
 }
 
@@ -347,74 +444,118 @@ template hipError_t launch_mask_shear<float>(long long, const float*, const floa
 template hipError_t launch_mask_shear<double>(long long, const double*, const double*,
                                               const unsigned char*, double*, double*, hipStream_t);
 
+static unsigned blocks256(long long count) { return (unsigned)((count + 255) / 256); }
+
+// One scale as a tile launch over `maps` maps (signal) or a.nb realisations.
+template <typename T, bool NOISE, int KC>
+static hipError_t launch_bc_scale_kc(const BcArgs<T>& a, int maps, hipStream_t s) {
+    const int rows = (a.ny + a.d - 1) / a.d;  // rows of the largest residue class
+    const int row_tiles = (rows + kBcTH - 1) / kBcTH;
+    const dim3 grid((a.nx + 63) / 64, a.d * row_tiles, NOISE ? 1 : maps);
+    const size_t lds = (size_t)(kBcTH + 4) * (64 + 4 * a.d + 64) * sizeof(T);
+    if (64 + 4 * a.d > 64 * KC || lds > 64 * 1024) return hipErrorInvalidConfiguration;
+    AMAP_LAUNCH(NOISE ? "noise_bc_tile" : "starlet_bc_tile", s, k_bc_scale<T, NOISE, KC><<<grid, 256, lds, s>>>(a));
+    return hipGetLastError();
+}
+template <typename T, bool NOISE>
+static hipError_t launch_bc_scale(const BcArgs<T>& a, int maps, hipStream_t s) {
+    if (a.d <= 16) return launch_bc_scale_kc<T, NOISE, 2>(a, maps, s);
+    if (a.d <= 32) return launch_bc_scale_kc<T, NOISE, 3>(a, maps, s);
+    if (a.d <= 64) return launch_bc_scale_kc<T, NOISE, 5>(a, maps, s);
+    return launch_bc_scale_kc<T, NOISE, 9>(a, maps, s);
+}
+
+int bc_tile_scales(int J, size_t elem) {
+    int jt = 0;
+    while (jt + 1 < J && (1 << jt) <= (elem == 4 ? bc_max_d<float>() : bc_max_d<double>())) ++jt;
+    return jt;
+}
+
 template <typename T>
 hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T* planes, T* tmp,
                              int maps, long long image_stride, long long planes_stride, hipStream_t s) {
     const long long plane = (long long)ny * nx;
     T* coarse = planes + (long long)(J - 1) * plane;
-    // scales 1 .. jt (dilation <= bc_max_d) run as tiles, alternating their
-    // c_j between tmp and the coarse plane so that c_jt lands in the coarse
-    // plane; the later scales run a row and a column pass in place there
-    int jt = 0;
-    while (jt + 1 < J && (1 << jt) <= bc_max_d<T>()) ++jt;
-    const T* c_prev = image;
-    long long cp_stride = image_stride;
+    // scales 1 .. jt run as tiles, alternating their c_j between tmp and the
+    // coarse plane so that c_jt lands in the coarse plane; the later scales
+    // run a row and a column pass in place there
+    const int jt = bc_tile_scales(J, sizeof(T));
+    BcArgs<T> a{};
+    a.c_prev = image;
+    a.cp_stride = image_stride;
+    a.ny = ny; a.nx = nx; a.mode = mode; a.w_stride = planes_stride;
     for (int j = 1; j <= jt; ++j) {
-        const int d = 1 << (j - 1);
         const bool to_coarse = ((jt - j) & 1) == 0;
-        T* dst = to_coarse ? coarse : tmp;
-        const long long dst_stride = to_coarse ? planes_stride : plane;
-        const int rows = (ny + d - 1) / d;  // rows of the largest residue class
-        const int row_tiles = (rows + kBcTH - 1) / kBcTH;
-        const dim3 grid((nx + kBcTW - 1) / kBcTW, d * row_tiles, maps);
-        const size_t lds = (size_t)(kBcTH + 4) * (kBcTW + 4 * d + kBcTW) * sizeof(T);
-        AMAP_LAUNCH("starlet_bc_tile", s,
-                    k_bc_scale_tile<T><<<grid, 256, lds, s>>>(c_prev, planes + (long long)(j - 1) * plane,
-                                                              dst, ny, nx, d, mode, cp_stride, dst_stride,
-                                                              planes_stride));
-        c_prev = dst;
-        cp_stride = dst_stride;
+        a.d = 1 << (j - 1);
+        a.c_next = to_coarse ? coarse : tmp;
+        a.cn_stride = to_coarse ? planes_stride : plane;
+        a.w = planes + (long long)(j - 1) * plane;
+        const hipError_t e = launch_bc_scale<T, false>(a, maps, s);
+        if (e != hipSuccess) return e;
+        a.c_prev = a.c_next;
+        a.cp_stride = a.cn_stride;
     }
     const dim3 grid((nx + 255) / 256, ny, maps);
     for (int j = jt + 1; j < J; ++j) {
         const int d = 1 << (j - 1);
         AMAP_LAUNCH("starlet_bc_row", s,
-                    k_bc_row<T><<<grid, 256, 0, s>>>(c_prev, tmp, nx, d, mode, cp_stride, plane));
+                    k_bc_row<T><<<grid, 256, 0, s>>>(a.c_prev, tmp, nx, d, mode, a.cp_stride, plane));
         AMAP_LAUNCH("starlet_bc_col", s,
-                    k_bc_col<T><<<grid, 256, 0, s>>>(tmp, c_prev, planes + (long long)(j - 1) * plane,
-                                                     coarse, ny, nx, d, mode, plane, cp_stride,
-                                                     planes_stride));
-        c_prev = coarse;
-        cp_stride = planes_stride;
+                    k_bc_col<T><<<grid, 256, 0, s>>>(tmp, a.c_prev, planes + (long long)(j - 1) * plane,
+                                                     coarse, ny, nx, d, mode, plane, a.cp_stride,
+                                                     planes_stride, planes_stride));
+        a.c_prev = coarse;
+        a.cp_stride = planes_stride;
     }
     return hipGetLastError();
 }
-static unsigned blocks256(long long count) { return (unsigned)((count + 255) / 256); }
 
 template <typename T>
-hipError_t launch_welford_bc(const T* w, long long w_stride, int nb, double* M, double* M2,
-                             long long count, int r0, hipStream_t s) {
-    AMAP_LAUNCH("welford_bc", s,
-                k_welford_bc<T><<<blocks256(count), 256, 0, s>>>(w, w_stride, nb, M, M2, count, r0));
+hipError_t launch_noise_bc(int ny, int nx, int J, int mode, T* kappa, T* tmp, T* row, T* wpl, int nb, int r0,
+                           int R, double* M, double* M2, const T* w_signal, T* sigma, T* snr, hipStream_t s) {
+    const long long plane = (long long)ny * nx, count = plane;
+    const int jt = bc_tile_scales(J, sizeof(T));
+    BcArgs<T> a{};
+    a.ny = ny; a.nx = nx; a.mode = mode; a.nb = nb; a.r0 = r0; a.R = R;
+    a.cp_stride = a.cn_stride = plane;
+    T* cur = kappa;
+    T* nxt = tmp;
+    for (int j = 1; j < J; ++j) {
+        const long long o = (long long)(j - 1) * plane;
+        if (j <= jt) {
+            a.d = 1 << (j - 1);
+            a.c_prev = cur;
+            a.c_next = j + 1 < J ? nxt : nullptr;
+            a.M = M + o; a.M2 = M2 + o;
+            a.w_signal = w_signal ? w_signal + o : nullptr;
+            a.sigma = sigma + o;
+            a.snr = snr ? snr + o : nullptr;
+            const hipError_t e = launch_bc_scale<T, true>(a, 1, s);
+            if (e != hipSuccess) return e;
+            T* t = cur; cur = nxt; nxt = t;
+            continue;
+        }
+        // larger dilations: row and column passes in place, then the update
+        const int d = 1 << (j - 1);
+        const dim3 grid((nx + 255) / 256, ny, nb);
+        AMAP_LAUNCH("starlet_bc_row", s, k_bc_row<T><<<grid, 256, 0, s>>>(cur, row, nx, d, mode, plane, plane));
+        AMAP_LAUNCH("starlet_bc_col", s,
+                    k_bc_col<T><<<grid, 256, 0, s>>>(row, cur, wpl, cur, ny, nx, d, mode, plane, plane, plane,
+                                                     plane));
+        AMAP_LAUNCH("welford_bc", s,
+                    k_welford_bc<T><<<blocks256(count), 256, 0, s>>>(wpl, plane, nb, M + o, M2 + o, count, r0));
+        if (r0 + nb == R)
+            AMAP_LAUNCH("sigma_snr_bc", s,
+                        k_sigma_snr_bc<T><<<blocks256(count), 256, 0, s>>>(
+                            M2 + o, R, w_signal ? w_signal + o : nullptr, sigma + o, snr ? snr + o : nullptr, count));
+    }
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_sigma_snr_bc(const double* M2, int R, const T* w_signal, T* sigma, T* snr,
-                               long long count, hipStream_t s) {
-    AMAP_LAUNCH("sigma_snr_bc", s,
-                k_sigma_snr_bc<T><<<blocks256(count), 256, 0, s>>>(M2, R, w_signal, sigma, snr, count));
-    return hipGetLastError();
-}
-
-#define AMAP_BOUNDED_NOISE(T)                                                                            \
-    template hipError_t launch_welford_bc<T>(const T*, long long, int, double*, double*, long long, int, \
-                                             hipStream_t);                                               \
-    template hipError_t launch_sigma_snr_bc<T>(const double*, int, const T*, T*, T*, long long, hipStream_t);
-AMAP_BOUNDED_NOISE(float)
-AMAP_BOUNDED_NOISE(double)
-#undef AMAP_BOUNDED_NOISE
-
+template hipError_t launch_noise_bc<float>(int, int, int, int, float*, float*, float*, float*, int, int, int,
+                                           double*, double*, const float*, float*, float*, hipStream_t);
+template hipError_t launch_noise_bc<double>(int, int, int, int, double*, double*, double*, double*, int, int,
+                                            int, double*, double*, const double*, double*, double*, hipStream_t);
 template hipError_t launch_starlet_bc<float>(int, int, int, int, const float*, float*, float*, int,
                                              long long, long long, hipStream_t);
 template hipError_t launch_starlet_bc<double>(int, int, int, int, const double*, double*, double*, int,
