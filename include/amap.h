@@ -121,9 +121,9 @@ amap_status amap_set_autotune(amap_ctx_t ctx, int enable);
  * pass, kind], ...]}, ...].  Every scale from j0 on couples only pixels
  * congruent mod d = 2^(j0-1) (the a-trous dilations, Sec. 2.3), so the d^2
  * sub-grids of such pixels are independent periodic images of side n / d.
- * kind 0: an LDS tile stage; kind 1 (noise statistics, the last stage): a
- * final stage on whole sub-grids, one per workgroup (width and sub-rows are
- * the sub-grid side); kind 2 (noise statistics): a tile stage on the
+ * kind 0: an LDS tile stage; kind 1 (the last stage): a final stage on whole
+ * sub-grids, one (noise statistics) or a strip of adjacent ones (signal) per
+ * workgroup (width and sub-rows are the sub-grid side); kind 2 (noise statistics): a tile stage on the
  * sub-grids of d taken as images, with the tile of an (n/d) x (n/d) map's
  * first stage; it follows a kind-0 or kind-2 stage and is the last stage or
  * followed by a kind-2 or kind-1 stage (each such stage lays out the

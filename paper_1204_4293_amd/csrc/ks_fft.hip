@@ -635,7 +635,7 @@ static hipError_t cols_inv_w(const KsArgs<T>& a) {
 //                  4096^2 x 8: 672 / 360
 //   forward pass:  rotating, 1024^2 x 128: 315 / 400; 2048^2 x 32: 430 / 488;
 //                  4096^2 x 8: 998 / 816
-//                  one map of 2048^2: 41 / 22; of 4096^2: 112 / 129
+//                  one map of 2048^2: 41 / 22, five: 90 / 113; one of 4096^2: 112 / 129
 //                  rotating, 1000 x 1000 in 2048^2 x 15: 154 / 131
 // Double precision from 1024 points (whose per-thread DFTs would not fit the
 // registers) has three-step kernels only.
@@ -651,8 +651,11 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
     if constexpr (fwd3_always<T, LOGN, CROP>()) {
         return launch_ks3_fwd<T, LOGN, CROP>(a);
     } else {
-        if constexpr (LOGN >= 11) {
-            if (a.rotate == (LOGN == 12)) return launch_ks3_fwd<T, LOGN, CROP>(a);
+        if constexpr (LOGN == 12) {
+            if (a.rotate) return launch_ks3_fwd<T, LOGN, CROP>(a);
+        }
+        if constexpr (LOGN == 11) {  // until 16-column strips fill the chip
+            if (!a.rotate && (1 << LOGN) / 16 * a.batch < 512) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
         constexpr int N = 1 << LOGN, WF = StripF<T, LOGN>::W;
         const int w = strip_width(N, CROP ? a.nx : N, a.batch, WF);

@@ -609,6 +609,115 @@ __global__ void __launch_bounds__(NT) k_starlet_stage(StageArgs<T> a) {
         store_owned<T, NT, kVecPerThread>(a.cout + (long long)map * a.cout_stride, g, prev);
 }
 
+// Write mode, final stage on whole sub-grids.  From scale j0 on, every tap of
+// every remaining scale stays inside one sub-grid of d0 = 2^(j0-1)
+// (subgrid_index): an m x m periodic map, m = n / d0, with dilations 1, 2, ..
+// A workgroup takes W sub-grids of adjacent columns p0 .. p0 + W - 1 and one
+// row residue q, so that its accesses are W-element runs of the rows, and
+// runs all remaining scales on them: no halo, and c read and written once
+// for all scales where single-scale tiles at these dilations read two to
+// four times their pixels.  The values live in LDS once, element (y', x', c)
+// at (y' m + x') W + c; a thread owns V vectors of one (x', c) in rows NT /
+// (m W / G) apart, and a pass's results wait in its registers until every
+// read is done.  Bound by memory traffic; 2048^2 float x 5 maps, scales 6-8 in
+// 107 us (199 as three tile stages); 2048^2 double, one map: 38 us (109).
+template <typename T>
+struct StripArgs {
+    int logn, j0, ns;
+    const T* src;
+    long long src_stride;
+    T* planes;
+    long long planes_stride;
+    int plane_base;
+    T* cout;
+    long long cout_stride;
+    const long long* src_off;     // as in StageArgs
+    const long long* planes_off;
+    int cout_plane;
+};
+template <typename T, int LOGM, int LOGW>
+struct StripGeom {
+    static constexpr int M = 1 << LOGM, W = 1 << LOGW, G = Vec<T>::G;
+    static constexpr int VECS = M * M * W / G;
+    static constexpr int NT = VECS / 8 < 1024 ? VECS / 8 : 1024;
+    static constexpr int V = VECS / NT;
+    static constexpr int ROWV = M * W / G;     // vectors of a row y'
+    static constexpr int STEP = NT / ROWV;     // rows between a thread's vectors
+    static constexpr size_t LDS = (size_t)M * M * W * sizeof(T);
+    static_assert(W >= G && NT % ROWV == 0 && V >= 1, "a thread's vectors lie in one (x', c)");
+};
+
+template <typename T, int LOGM, int LOGW>
+__global__ void __launch_bounds__((StripGeom<T, LOGM, LOGW>::NT))
+k_starlet_strip(StripArgs<T> a) {
+    using S = StripGeom<T, LOGM, LOGW>;
+    constexpr int M = S::M, W = S::W, G = S::G, NT = S::NT, V = S::V, ROWV = S::ROWV, STEP = S::STEP;
+    using VA = VArr<T, G>;
+    extern __shared__ __align__(16) unsigned char strip_smem[];
+    T* A = reinterpret_cast<T*>(strip_smem);
+    const int logd = a.logn - LOGM, strips = (1 << logd) >> LOGW;
+    const long long n2 = 1ll << (2 * a.logn);
+    // strip fastest, then the row residue; consecutive ones on one XCD, where
+    // their runs share cache lines
+    const int total = gridDim.x;
+    int t = blockIdx.x;
+    if ((total & 7) == 0) t = (t & 7) * (total >> 3) + (t >> 3);
+    const int p0 = (t % strips) * W, q = t / strips;
+    const int map = blockIdx.y;
+    const T* src = a.src + (a.src_off ? a.src_off[map] : (long long)map * a.src_stride);
+    T* planes = a.planes + (a.planes_off ? a.planes_off[map] : (long long)map * a.planes_stride);
+    const int cv = (threadIdx.x % (W / G)) * G, xs = (threadIdx.x / (W / G)) & (M - 1);
+    const int y0 = threadIdx.x / ROWV;
+    const auto global = [&](int k) {  // offset of vector k in a plane
+        return ((long long)(q + ((y0 + k * STEP) << logd)) << a.logn) + p0 + cv + (xs << logd);
+    };
+    VA prev[V], o[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) prev[k] = vload<T, G>(src + global(k));
+    const auto lds = [&](int y, int x) { return A + ((y << LOGM) + x) * W + cv; };
+#pragma unroll
+    for (int k = 0; k < V; ++k) vstore<T, G>(lds(y0 + k * STEP, xs), prev[k]);
+    __syncthreads();
+    for (int s = 0; s < a.ns; ++s) {
+        const int d = 1 << s;
+        const int xm2 = (xs - 2 * d) & (M - 1), xm1 = (xs - d) & (M - 1), xp1 = (xs + d) & (M - 1),
+                  xp2 = (xs + 2 * d) & (M - 1);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const int y = y0 + k * STEP;
+            o[k] = vrow<T, G>(vload<T, G>(lds(y, xm2)), vload<T, G>(lds(y, xm1)), vload<T, G>(lds(y, xs)),
+                              vload<T, G>(lds(y, xp1)), vload<T, G>(lds(y, xp2)));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < V; ++k) vstore<T, G>(lds(y0 + k * STEP, xs), o[k]);
+        __syncthreads();
+        T* wp = planes + (long long)(a.j0 + s - 1 - a.plane_base) * n2;
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            const int y = y0 + k * STEP;
+            o[k] = vcol<T, G>(vload<T, G>(lds((y - 2 * d) & (M - 1), xs)), vload<T, G>(lds((y - d) & (M - 1), xs)),
+                              vload<T, G>(lds(y, xs)), vload<T, G>(lds((y + d) & (M - 1), xs)),
+                              vload<T, G>(lds((y + 2 * d) & (M - 1), xs)));
+            VA w;
+#pragma unroll
+            for (int c = 0; c < G; ++c) w.e[c] = prev[k].e[c] - o[k].e[c];
+            vstore<T, G>(wp + global(k), w);
+            prev[k] = o[k];
+        }
+        if (s + 1 < a.ns) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < V; ++k) vstore<T, G>(lds(y0 + k * STEP, xs), prev[k]);
+            __syncthreads();
+        }
+    }
+    T* c = a.cout_plane >= 0 ? planes + (long long)a.cout_plane * n2
+                             : a.cout + (long long)map * a.cout_stride;
+#pragma unroll
+    for (int k = 0; k < V; ++k) vstore<T, G>(c + global(k), prev[k]);
+}
+
 // Noise mode: each workgroup owns one tile and takes the realisations
 // b = group, group + groups, ... of the batch in turn, prefetching the next
 // realisation's tile into registers while the current one is processed.
@@ -1358,6 +1467,47 @@ static bool subgrid_ok(int n, int j0, int J) {
     return m >= 16 && m <= (sizeof(T) == 4 ? 64 : 32);
 }
 
+// Final write-mode stages on whole sub-grids: all scales from j0 on, on
+// sub-grids of side 32 or 64, in strips of 32 bytes (side 64) or 64 bytes of
+// columns, at least one strip per row residue.
+template <typename T>
+constexpr int strip_logw(int logm) { return (logm == 6 ? 3 : 4) - (sizeof(T) == 8 ? 1 : 0); }
+template <typename T>
+static bool strip_ok(int n, int j0, int J) {
+    if (j0 < 2 || J - j0 < 1) return false;
+    const int d0 = 1 << (j0 - 1), m = n / d0;
+    return (m == 32 && d0 >= (1 << strip_logw<T>(5))) || (m == 64 && d0 >= (1 << strip_logw<T>(6)));
+}
+
+template <typename T, int LOGM>
+static hipError_t launch_strip_m(const StripArgs<T>& a, int maps, hipStream_t s) {
+    constexpr int LOGW = strip_logw<T>(LOGM);
+    using S = StripGeom<T, LOGM, LOGW>;
+    static_assert(S::LDS <= (size_t)kLdsBytes, "a strip fits LDS");
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_starlet_strip<T, LOGM, LOGW>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int logd = a.logn - LOGM;
+    if (logd < LOGW || logd != a.j0 - 1) return hipErrorInvalidConfiguration;
+    static const char* names[12] = {"starlet_stage_j1", "starlet_stage_j2", "starlet_stage_j3",
+                                    "starlet_stage_j4", "starlet_stage_j5", "starlet_stage_j6",
+                                    "starlet_stage_j7", "starlet_stage_j8", "starlet_stage_j9",
+                                    "starlet_stage_j10", "starlet_stage_j11", "starlet_stage_j12"};
+    AMAP_LAUNCH(names[a.j0 - 1 < 12 ? a.j0 - 1 : 11], s,
+                k_starlet_strip<T, LOGM, LOGW><<<dim3(1u << (2 * logd - LOGW), maps), S::NT, S::LDS, s>>>(a));
+    return hipGetLastError();
+}
+template <typename T>
+static hipError_t launch_strip(const StripArgs<T>& a, int maps, hipStream_t s) {
+    if (a.logn - (a.j0 - 1) == 5) return launch_strip_m<T, 5>(a, maps, s);
+    if (a.logn - (a.j0 - 1) == 6) return launch_strip_m<T, 6>(a, maps, s);
+    return hipErrorInvalidValue;
+}
+
 // A noise tile stage on the sub-grids of d0 = 2^(j0-1) as periodic images
 // of side m = n / d0: the geometry of the tile (tw, th, rb) of an m x m
 // map's first stage of ns scales.  False if the planner offers no such tile.
@@ -1511,8 +1661,9 @@ bool plan_valid(int n, int J, bool noise, const StagePlan& plan) {
         const StagePlan::Stage& t = plan.st[k];
         if (t.j0 != j || t.ns < 1 || t.j0 + t.ns > J) return false;
         if (t.kind == kStageSubgrid) {
-            if (!noise || k + 1 != plan.nstages || t.j0 + t.ns != J || !subgrid_ok<T>(n, t.j0, J) ||
-                (t.rb != 1 && t.rb != 2) || t.tw != (n >> (t.j0 - 1)) || t.th != t.tw)
+            if (k + 1 != plan.nstages || t.j0 + t.ns != J || t.tw != (n >> (t.j0 - 1)) || t.th != t.tw ||
+                !(noise ? subgrid_ok<T>(n, t.j0, J) && (t.rb == 1 || t.rb == 2)
+                        : strip_ok<T>(n, t.j0, J) && t.rb == 1))
                 return false;
         } else if (t.kind == kStageImages) {
             // after a plain tile stage or another such stage; the last stage or
@@ -1550,9 +1701,10 @@ static hipError_t resolve_stages(int n, int J, bool acc, const StagePlan* p, Sta
         for (int k = 0; k < p->nstages; ++k) {
             const StagePlan::Stage& t = p->st[k];
             StageGeom g{};
-            if (t.kind == kStageSubgrid) {  // a final noise stage on whole sub-grids
-                if (!acc || k + 1 != p->nstages || t.j0 + t.ns != J || !subgrid_ok<T>(n, t.j0, J) ||
-                    (t.rb != 1 && t.rb != 2))
+            if (t.kind == kStageSubgrid) {  // a final stage on whole sub-grids
+                if (k + 1 != p->nstages || t.j0 + t.ns != J ||
+                    !(acc ? subgrid_ok<T>(n, t.j0, J) && (t.rb == 1 || t.rb == 2)
+                          : strip_ok<T>(n, t.j0, J) && t.rb == 1))
                     return hipErrorInvalidValue;
                 g.rb = t.rb;
                 run[nstages++] = StageRun{t.j0, t.ns, g, false, true, false};
@@ -1636,7 +1788,15 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
         const T* cur = a.kappa_off ? nullptr : a.kappa;  // keeps the first stage's output off its input
         for (int gi = 0; gi < nstages; ++gi) {
             const StageRun& st = plan[gi];
-            if (!st.tiled) return hipErrorNotSupported;
+            if (!st.tiled && !st.sub) return hipErrorNotSupported;
+            if (st.sub) {  // the last stage
+                StripArgs<T> s;
+                s.logn = a.logn; s.j0 = st.j0; s.ns = st.ns;
+                s.src = gi == 0 ? a.kappa : cur; s.src_stride = n2; s.src_off = gi == 0 ? a.kappa_off : nullptr;
+                s.planes = a.planes; s.planes_stride = 0; s.planes_off = a.planes_off; s.plane_base = 0;
+                s.cout = nullptr; s.cout_stride = n2; s.cout_plane = a.J - 1;
+                return launch_strip<T>(s, a.batch, a.stream);
+            }
             const bool last = st.j0 + st.ns == a.J;
             int lt = 0;
             while ((1 << lt) < st.g.tw) ++lt;
@@ -1702,7 +1862,15 @@ hipError_t launch_starlet(const StarletArgs<T>& a) {
         hipError_t e;
         int lt = 0;
         while ((1 << lt) < st.g.tw) ++lt;
-        if (st.sub) {  // acc only, the last stage: c and the statistics in sub-grid order
+        if (st.sub && !acc) {  // the last stage
+            StripArgs<T> s;
+            s.logn = a.logn; s.j0 = st.j0; s.ns = st.ns;
+            s.src = cur; s.src_stride = cur_stride; s.src_off = nullptr;
+            s.planes = wdst; s.planes_stride = wstride; s.planes_off = nullptr; s.plane_base = pbase;
+            s.cout = dst; s.cout_stride = dst_stride; s.cout_plane = -1;
+            return launch_strip<T>(s, a.batch, a.stream);
+        }
+        if (st.sub) {  // the last stage: c and the statistics in sub-grid order
             // (after a stage on sub-grid images, their sub-grids image by image)
             const int tiles = noise_tiles(n, st);
             NoiseSubArgs<T> s;
@@ -1871,7 +2039,8 @@ hipError_t tune_starlet(const StarletArgs<T>& a, int reps, StagePlan* out) {
         best[j] = img[j] = sub[j] = -1.f;
         then_images[j] = false;
         img_next[j] = 0;
-        for (int rb = 1; rb <= 2 && acc && e == hipSuccess && subgrid_ok<T>(n, j, J); ++rb) {
+        for (int rb = 1; rb <= (acc ? 2 : 1) && e == hipSuccess &&
+                         (acc ? subgrid_ok<T>(n, j, J) : strip_ok<T>(n, j, J)); ++rb) {
             // all remaining scales on whole sub-grids (a final stage)
             const int m = n >> (j - 1);
             const StagePlan::Stage st{j, J - j, m, m, rb, kStageSubgrid};
