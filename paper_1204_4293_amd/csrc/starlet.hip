@@ -1254,18 +1254,23 @@ struct StageGeom {
 // Most tile candidates of one stage (tile widths x heights x pass widths).
 constexpr int kMaxCand = 64;
 
-// Largest tile overhead accepted for a stage (LDS elements per output pixel).
+// Largest tile overhead accepted for a stage (LDS elements per output pixel),
+// and, for the tuner, of write-mode stages: launches that leave most of the
+// chip idle are faster on many small tiles than on few with little halo.
 constexpr double kMaxHaloRatio = 2.6;
+constexpr double kMaxHaloRatioTuned = 5.0;
 
 // Tiles for a stage of ns scales from j0 whose two LDS buffers fit and whose
 // halo overhead is bounded, best first (smallest overhead, then least LDS);
 // noise stages also need the tile to fit the prefetch registers and one
 // owned vector per thread.  Float noise stages of one or two scales with one
 // owned vector per thread are also offered with two realisations per LDS
-// pass (twice the LDS, fewer barriers per realisation).  Returns the number
-// written to out (at most cap).
+// pass (twice the LDS, fewer barriers per realisation).  The analytic planner
+// (tuned = false) takes the first.  Returns the number written to out (at
+// most cap).
 template <typename T>
-static int stage_candidates(int n, int j0, int ns, bool noise, StageGeom* out, int cap) {
+static int stage_candidates(int n, int j0, int ns, bool noise, bool tuned, StageGeom* out, int cap) {
+    const double most = tuned && !noise ? kMaxHaloRatioTuned : kMaxHaloRatio;
     constexpr int G = Vec<T>::G;
     const int d0 = 1 << (j0 - 1);
     const int Hx = stage_hx(d0, ns, G), Hv = 2 * ((1 << ns) - 1);
@@ -1290,7 +1295,7 @@ static int stage_candidates(int n, int j0, int ns, bool noise, StageGeom* out, i
             const size_t lds = 2 * (size_t)(TXT + 2 * G) * TVT * sizeof(T) + G * sizeof(T);
             if (lds > (size_t)kLdsBytes) continue;
             const double r = (double)TXT * TVT / ((double)tw * th);
-            if (r > kMaxHaloRatio && !(ns == 1 && r <= 2 * kMaxHaloRatio)) continue;
+            if (r > most && !(ns == 1 && r <= 2 * kMaxHaloRatio)) continue;
             int nt = tw * th / (G * kVecPerThread);
             nt = nt < 256 ? 256 : (nt > 512 ? 512 : nt);
             if (!noise && tw * th > nt * G * kVecPerThread) continue;  // write kernel: 2 vectors per thread
@@ -1324,7 +1329,7 @@ static int stage_candidates(int n, int j0, int ns, bool noise, StageGeom* out, i
 template <typename T>
 static bool pick_stage(int n, int j0, int left, bool noise, StageGeom* g) {
     for (int ns = left < 3 ? left : 3; ns >= 1; --ns)
-        if (stage_candidates<T>(n, j0, ns, noise, g, 1) == 1) return true;
+        if (stage_candidates<T>(n, j0, ns, noise, false, g, 1) == 1) return true;
     return false;
 }
 
@@ -1333,7 +1338,7 @@ template <typename T>
 static bool stage_geom_of(int n, int j0, int ns, int tw, int th, int rb, bool noise,
                           StageGeom* g) {
     StageGeom all[kMaxCand];
-    const int m = stage_candidates<T>(n, j0, ns, noise, all, kMaxCand);
+    const int m = stage_candidates<T>(n, j0, ns, noise, true, all, kMaxCand);
     for (int i = 0; i < m; ++i)
         if (all[i].tw == tw && all[i].th == th && all[i].rb == rb) {
             *g = all[i];
@@ -2005,14 +2010,22 @@ hipError_t tune_starlet(const StarletArgs<T>& a, int reps, StagePlan* out) {
         return r;
     };
     // the two best tiles (least halo overhead) of each thread configuration
-    // (threads, owned vectors, realisations per pass) of a stage of ns
-    // scales from j0 of an m x m map
+    // (threads, owned vectors, realisations per pass) of a stage of ns scales
+    // from j0 of an m x m map.  Signals of at most kFewPixels are tried on two
+    // tiles of each size instead: with at most one workgroup per CU a stage
+    // takes as long as one tile, and the smallest wins although its halo is
+    // up to 4 times its pixels (256^2 double, scales 1-2 / 3-4: 7.7 / 6.6 us
+    // on the least-halo tiles, 5.4 / 6.4 us on 16 x 16 and 32 x 16).  From
+    // 1024^2 the least-halo tiles are the fastest (8.7 against 13 us on
+    // 32 x 16), so there the search stays short.
+    constexpr long long kFewPixels = 1ll << 18;
+    const bool few = !acc && ((long long)a.batch << (2 * a.logn)) <= kFewPixels;
     auto candidates = [&](int m, int j0, int ns, StageGeom* cand) {
         StageGeom all[kMaxCand];
-        const int na = stage_candidates<T>(m, j0, ns, acc, all, kMaxCand);
+        const int na = stage_candidates<T>(m, j0, ns, acc, true, all, kMaxCand);
         auto config = [&](const StageGeom& sg) {
             const NoiseCfg cfg = noise_cfg(sg.tw * sg.th / Vec<T>::G);
-            return acc ? (cfg.nt * 8 + cfg.kv) * 4 + sg.rb : sg.nt;
+            return acc ? (cfg.nt * 8 + cfg.kv) * 4 + sg.rb : few ? sg.tw * sg.th : sg.nt;
         };
         int nc = 0;
         for (int i = 0; i < na && nc < 24; ++i) {
