@@ -136,15 +136,21 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
                     const int f0 = (y0 + yl) * nx + x0;            // flat index of the segment
                     const int oct = (f0 >> 3) + (o - yl * OCT);
                     if (8 * oct >= f0 + wv) continue;
+                    T gp[8], gq[8];  // on their way while the block is drawn
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int f = min(max(8 * oct + i, f0), f0 + wv - 1);
+                        gp[i] = a1[f];
+                        gq[i] = a2[f];
+                    }
                     uint32_t u[8];
                     philox_block_u32(seed, r, (uint64_t)oct, u);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         const int f = 8 * oct + i;
                         if (f < f0 || f >= f0 + wv) continue;
-                        T gp = a1[f], gq = a2[f];
-                        rotate_by_u32(u[i], gp, gq);
-                        buf[yl * W + (f - f0)] = make_cpx(gp, gq);
+                        rotate_by_u32(u[i], gp[i], gq[i]);
+                        buf[yl * W + (f - f0)] = make_cpx(gp[i], gq[i]);
                     }
                 }
             } else {
@@ -581,10 +587,16 @@ k_ks_cols_inv(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ 
 // ---- host launchers ------------------------------------------------------------
 // Strips as wide as leave a launch ~512 workgroups (cols columns of each of
 // `maps` maps), from wmax down to 4 columns (n = 256 and up: narrower maps
-// are small at any width).
-static int strip_width(int n, int cols, long long maps, int wmax) {
+// are small at any width).  Rotating strips draw random blocks of 8 pixels,
+// a strip of four each block twice and, in a cropped field, up to two for
+// four pixels: they stay at 8 columns and leave 128 workgroups.  Measured
+// (us of all noise passes, float, 4 / 8 / 16 columns): 512^2 x 8 realisations 85 / 73 /
+// 74; 1024^2 x 2: 101 / 92 / 94, x 4: 142 / 121 / 120; 1000^2 field x 2: 139 /
+// 129 / 133, x 4: 210 / 188 / 181.
+static int strip_width(int n, int cols, long long maps, int wmax, bool rotate) {
+    const int least = rotate ? 8 : 4;
     int w = wmax;
-    while (n >= 256 && w > 4 && (cols + w - 1) / w * maps < 512) w /= 2;
+    while (n >= 256 && w > least && (cols + w - 1) / w * maps < (rotate ? 128 : 512)) w /= 2;
     return w;
 }
 
@@ -658,7 +670,7 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
             if (!a.rotate && (1 << LOGN) / 16 * a.batch < 512) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
         constexpr int N = 1 << LOGN, WF = StripF<T, LOGN>::W;
-        const int w = strip_width(N, CROP ? a.nx : N, a.batch, WF);
+        const int w = strip_width(N, CROP ? a.nx : N, a.batch, WF, a.rotate);
         if constexpr (WF >= 16) {
             if (w == 16) return cols_fwd_w<T, LOGN, CROP, 16>(a);
         }
@@ -694,7 +706,7 @@ static hipError_t ks_inv(const KsArgs<T>& a) {
         return launch_ks3_inv<T, LOGN, CROP>(a);
     } else {
         constexpr int N = 1 << LOGN, WI = StripI<T, LOGN>::W;
-        const int w = strip_width(N, CROP ? (a.nx + 1) / 2 : N / 2, a.batch, WI);
+        const int w = strip_width(N, CROP ? (a.nx + 1) / 2 : N / 2, a.batch, WI, false);
         if constexpr (WI >= 16) {
             if (w == 16) return cols_inv_w<T, LOGN, CROP, 16>(a);
         }
