@@ -217,13 +217,15 @@ hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T*
 
 // Scales of a J-plane transform that run as tiles (the rest need scratch).
 int bc_tile_scales(int J, size_t elem);
+// Detail planes per realisation that launch_noise_bc stores (wpl).
+int bc_noise_details(int ny, int nx, int J, size_t elem);
 // Noise statistics of nb realisations' ny x nx kappa maps (realisations r0 ..
 // r0+nb-1 of R, packed, overwritten): every detail plane's running mean and
 // squared deviations continue in M and M2 ([J-1][ny][nx], double; Welford's
 // update in order, realisation 0 writes them unread) and, with the last
 // realisation, end as sigma = sqrt(M2/(R-1)) and, if snr is not null,
 // snr = w_signal / sigma (0 where sigma = 0).  Scratch of nb*ny*nx each: tmp,
-// and, if not every scale runs as tiles, row and wpl.
+// row if not every scale runs as tiles, and bc_noise_details planes at wpl.
 template <typename T>
 hipError_t launch_noise_bc(int ny, int nx, int J, int mode, T* kappa, T* tmp, T* row, T* wpl, int nb, int r0,
                            int R, double* M, double* M2, const T* w_signal, T* sigma, T* snr, hipStream_t s);

@@ -908,14 +908,16 @@ amap_status amap_mask_shear(amap_ctx_t c, amap_dtype dt, int ny, int nx, const u
 }  // extern "C"
 
 // Field-sized buffers per realisation of the bounded noise path: kappa and
-// the coarse plane beside it, and, for dilations beyond the tiles, a row pass
-// and a detail plane.
-static size_t bounded_noise_fields(int J, size_t esz) { return bc_tile_scales(J, esz) == J - 1 ? 2 : 4; }
+// the coarse plane beside it, detail planes, and, for dilations beyond the
+// tiles, a row pass.
+static size_t bounded_noise_fields(int ny, int nx, int J, size_t esz) {
+    return 2 + bc_noise_details(ny, nx, J, esz) + (bc_tile_scales(J, esz) < J - 1 ? 1 : 0);
+}
 // Realisations per launch of the bounded noise path: as many as fit about
 // 1 GiB of workspace (a P^2 spectrum and the field-sized buffers each), 1 ..
 // 32, evened out over the batches that takes.
 static int bounded_noise_batch(int ny, int nx, int P, int J, size_t esz, int n_real) {
-    const size_t per = 2 * (size_t)P * P * esz + bounded_noise_fields(J, esz) * ny * nx * esz;
+    const size_t per = 2 * (size_t)P * P * esz + bounded_noise_fields(ny, nx, J, esz) * ny * nx * esz;
     size_t b = ((size_t)1 << 30) / per;
     if (b < 1) b = 1;
     if (b > 32) b = 32;
@@ -924,7 +926,7 @@ static int bounded_noise_batch(int ny, int nx, int P, int J, size_t esz, int n_r
 }
 static size_t bounded_noise_bytes(int ny, int nx, int P, int J, size_t esz, int B) {
     const size_t pp = (size_t)P * P * esz * B, ff = (size_t)ny * nx * esz * B;
-    return align256(2 * pp) + bounded_noise_fields(J, esz) * align256(ff) +
+    return align256(2 * pp) + bounded_noise_fields(ny, nx, J, esz) * align256(ff) +
            2 * align256((size_t)(J - 1) * ny * nx * 8);
 }
 
@@ -937,15 +939,17 @@ static amap_status enqueue_noise_bc(const amap_ctx* c, char* w, int ny, int nx, 
     const size_t ff = align256((size_t)fn * sizeof(T) * B);
     char* q = w;
     cpx<T>* C = reinterpret_cast<cpx<T>*>(q);  q += align256(2 * (size_t)pn * sizeof(T) * B);
-    T* field[4] = {nullptr, nullptr, nullptr, nullptr};
-    for (size_t k = 0; k < bounded_noise_fields(J, sizeof(T)); ++k, q += ff) field[k] = reinterpret_cast<T*>(q);
+    T* kap = reinterpret_cast<T*>(q);   q += ff;
+    T* tmp = reinterpret_cast<T*>(q);   q += ff;
+    T* row = reinterpret_cast<T*>(q);   q += bc_tile_scales(J, sizeof(T)) < J - 1 ? ff : 0;
+    T* wpl = reinterpret_cast<T*>(q);   q += bc_noise_details(ny, nx, J, sizeof(T)) * ff;
     double* M = reinterpret_cast<double*>(q);  q += align256((size_t)(J - 1) * fn * 8);
     double* M2 = reinterpret_cast<double*>(q);
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int nb = n_real - r0 < B ? n_real - r0 : B;
-        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, g1, g2, 0, C, field[0], nullptr, fn, true, seed, (uint64_t)r0, s,
+        AMAP_TRY(enqueue_ks<T>(c, ilog2(P), nb, g1, g2, 0, C, kap, nullptr, fn, true, seed, (uint64_t)r0, s,
                                ny, nx));
-        AMAP_HIP(launch_noise_bc<T>(ny, nx, J, boundary, field[0], field[1], field[2], field[3], nb, r0, n_real,
+        AMAP_HIP(launch_noise_bc<T>(ny, nx, J, boundary, kap, tmp, row, wpl, nb, r0, n_real,
                                     M, M2, planes_signal, sigma, snr, s),
                  "bounded noise kernels");
     }

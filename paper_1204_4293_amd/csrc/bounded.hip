@@ -241,40 +241,46 @@ k_bc_scale(BcArgs<T> a) {
     }
 }
 
-// Welford's update with realisations r0 .. r0+nb-1 in order, the b-th's
-// values at w + b w_stride (realisation 0 writes M and M2 unread).
+// Welford's update of one or more scales (blockIdx.y) with realisations
+// r0 .. r0+nb-1 in order, the b-th's detail plane at w + b w_stride, scale by
+// scale w_scale apart: the arithmetic of k_bc_scale's.  Realisation 0 starts
+// from nothing, the last one (r0 + nb = R) ends as sigma and S/N.
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_welford_bc(const T* __restrict__ w, long long w_stride, int nb, double* __restrict__ M,
-             double* __restrict__ M2, long long count, int r0) {
+k_bc_stats(const T* __restrict__ w, long long w_stride, long long w_scale, int nb, int r0, int R,
+           double* __restrict__ M, double* __restrict__ M2, const T* __restrict__ w_signal, T* __restrict__ sigma,
+           T* __restrict__ snr, long long count) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= count) return;
-    double m = r0 == 0 ? 0.0 : M[i], m2 = r0 == 0 ? 0.0 : M2[i];
-    for (int b = 0; b < nb; ++b) {
-        const double v = (double)w[b * w_stride + i];
-        const int r = r0 + b;
-        if (r == 0) {
-            m = v;
-            m2 = 0.0;
-            continue;
-        }
-        const double d = v - m, mn = m + d / (double)(r + 1);
-        m2 = m2 + d * (v - mn);
-        m = mn;
+    const long long o = blockIdx.y * count + i;
+    w += blockIdx.y * w_scale + i;
+    double mean = 0.0, m2 = 0.0;
+    if (r0 > 0) {
+        mean = M[o];
+        m2 = M2[o];
     }
-    M[i] = m;
-    M2[i] = m2;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256)
-k_sigma_snr_bc(const double* __restrict__ M2, int R, const T* __restrict__ w_signal, T* __restrict__ sigma,
-               T* __restrict__ snr, long long count) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
-    const double sg = sqrt(M2[i] / (double)(R - 1));
-    sigma[i] = (T)sg;
-    if (snr) snr[i] = sg > 0.0 ? (T)((double)w_signal[i] / sg) : (T)0;
+    constexpr int U = 8;  // values on their way at a time
+    for (int b0 = 0; b0 < nb; b0 += U) {
+        T v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) v[k] = w[(b0 + k < nb ? b0 + k : nb - 1) * w_stride];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (b0 + k >= nb) break;
+            const double inv = 1.0 / (double)(r0 + b0 + k + 1);
+            const double dl = (double)v[k] - mean;
+            mean = fma(dl, inv, mean);
+            m2 = fma(dl, (double)v[k] - mean, m2);
+        }
+    }
+    if (r0 + nb < R) {
+        M[o] = mean;
+        M2[o] = m2;
+        return;
+    }
+    const double sg = sqrt(m2 / (double)(R - 1));
+    sigma[o] = (T)sg;
+    if (snr) snr[o] = sg > 0.0 ? (T)((double)w_signal[o] / sg) : (T)0;
 }
 
 // Whether pixel idx of value v is a strict 8-neighbour maximum under the
@@ -444,8 +450,6 @@ template hipError_t launch_mask_shear<float>(long long, const float*, const floa
 template hipError_t launch_mask_shear<double>(long long, const double*, const double*,
                                               const unsigned char*, double*, double*, hipStream_t);
 
-static unsigned blocks256(long long count) { return (unsigned)((count + 255) / 256); }
-
 // One scale as a tile launch over `maps` maps (signal) or a.nb realisations.
 template <typename T, bool NOISE, int KC>
 static hipError_t launch_bc_scale_kc(const BcArgs<T>& a, int maps, hipStream_t s) {
@@ -510,29 +514,55 @@ hipError_t launch_starlet_bc(int ny, int nx, int J, int mode, const T* image, T*
     return hipGetLastError();
 }
 
+// Whether a field's realisations run side by side, their details stored, and
+// the statistics are taken in a pass of their own: where a scale's tiles are
+// few workgroups per CU, one realisation after the other in a tile takes
+// about 3 us each, however small the field.  Seven scales, apart / in the
+// tiles, us: 250^2 x 16 realisations (64 tiles) 81 / 277; 500^2 x 16 (256)
+// 174 / 317; 940 x 221 x 7 (236) 133 / 202; 700^2 x 16 (484) 371 / 421; 850^2
+// x 16 (756) 534 / 491; 1000^2 x 16 (1008) 617 / 516; in double precision 700^2
+// 600 / 672, 850^2 858 / 752.
+static bool bc_noise_apart(int ny, int nx) {
+    return (long long)((nx + 63) / 64) * ((ny + kBcTH - 1) / kBcTH) < 600;
+}
+int bc_noise_details(int ny, int nx, int J, size_t elem) {
+    const int jt = bc_tile_scales(J, elem);
+    return bc_noise_apart(ny, nx) ? jt : jt < J - 1 ? 1 : 0;
+}
+
 template <typename T>
 hipError_t launch_noise_bc(int ny, int nx, int J, int mode, T* kappa, T* tmp, T* row, T* wpl, int nb, int r0,
                            int R, double* M, double* M2, const T* w_signal, T* sigma, T* snr, hipStream_t s) {
-    const long long plane = (long long)ny * nx, count = plane;
+    const long long plane = (long long)ny * nx;
     const int jt = bc_tile_scales(J, sizeof(T));
+    const bool kept = bc_noise_apart(ny, nx);
     BcArgs<T> a{};
     a.ny = ny; a.nx = nx; a.mode = mode; a.nb = nb; a.r0 = r0; a.R = R;
-    a.cp_stride = a.cn_stride = plane;
+    a.cp_stride = a.cn_stride = a.w_stride = plane;
     T* cur = kappa;
     T* nxt = tmp;
+    const auto stats = [&](int j, int scales) {  // of scales j .. j + scales - 1, their details in wpl
+        const long long o = (long long)(j - 1) * plane;
+        AMAP_LAUNCH("noise_bc_stats", s,
+                    k_bc_stats<T><<<dim3((unsigned)((plane + 255) / 256), scales), 256, 0, s>>>(
+                        wpl, plane, nb * plane, nb, r0, R, M + o, M2 + o, w_signal ? w_signal + o : nullptr,
+                        sigma + o, snr ? snr + o : nullptr, plane));
+    };
     for (int j = 1; j < J; ++j) {
         const long long o = (long long)(j - 1) * plane;
         if (j <= jt) {
             a.d = 1 << (j - 1);
             a.c_prev = cur;
-            a.c_next = j + 1 < J ? nxt : nullptr;
+            a.c_next = kept || j + 1 < J ? nxt : nullptr;
+            a.w = kept ? wpl + (j - 1) * nb * plane : nullptr;
             a.M = M + o; a.M2 = M2 + o;
             a.w_signal = w_signal ? w_signal + o : nullptr;
             a.sigma = sigma + o;
             a.snr = snr ? snr + o : nullptr;
-            const hipError_t e = launch_bc_scale<T, true>(a, 1, s);
+            const hipError_t e = kept ? launch_bc_scale<T, false>(a, nb, s) : launch_bc_scale<T, true>(a, 1, s);
             if (e != hipSuccess) return e;
             T* t = cur; cur = nxt; nxt = t;
+            if (kept && j == jt) stats(1, jt);
             continue;
         }
         // larger dilations: row and column passes in place, then the update
@@ -542,12 +572,7 @@ hipError_t launch_noise_bc(int ny, int nx, int J, int mode, T* kappa, T* tmp, T*
         AMAP_LAUNCH("starlet_bc_col", s,
                     k_bc_col<T><<<grid, 256, 0, s>>>(row, cur, wpl, cur, ny, nx, d, mode, plane, plane, plane,
                                                      plane));
-        AMAP_LAUNCH("welford_bc", s,
-                    k_welford_bc<T><<<blocks256(count), 256, 0, s>>>(wpl, plane, nb, M + o, M2 + o, count, r0));
-        if (r0 + nb == R)
-            AMAP_LAUNCH("sigma_snr_bc", s,
-                        k_sigma_snr_bc<T><<<blocks256(count), 256, 0, s>>>(
-                            M2 + o, R, w_signal ? w_signal + o : nullptr, sigma + o, snr ? snr + o : nullptr, count));
+        stats(j, 1);
     }
     return hipGetLastError();
 }
