@@ -122,7 +122,7 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
         if constexpr (CROP) {
             const int wv = nx - x0 < W ? nx - x0 : W;              // the field's columns and
             const int yv = ny - y0 < ROWS ? ny - y0 : ROWS;        // rows in this phase
-            if (wv < W || yv < ROWS) {
+            if (ROTATE && (wv < W || yv < ROWS)) {
                 for (int e = threadIdx.x; e < ROWS * W; e += NT) buf[e] = make_cpx((T)0, (T)0);
                 __syncthreads();
             }
@@ -154,11 +154,20 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
                     }
                 }
             } else {
-                for (int e = threadIdx.x; e < yv * W; e += NT) {
-                    const int yl = e / W, cc = e % W;
-                    if (cc >= wv) continue;
-                    const int gi = (y0 + yl) * nx + x0 + cc;
-                    buf[e] = make_cpx(a1[gi], a2[gi]);
+                constexpr int ITER = ROWS * W / NT, U = ITER < 8 ? ITER : 8;  // U loads on their way at a time
+                static_assert(ROWS * W % NT == 0 && ITER % U == 0, "a phase's values spread evenly over the threads");
+                for (int i0 = 0; i0 < ITER; i0 += U) {
+                    cpx<T> v[U];
+#pragma unroll
+                    for (int i = 0; i < U; ++i) {
+                        const int e = threadIdx.x + (i0 + i) * NT, yl = e / W, cc = e % W;
+                        const bool in = yl < yv && cc < wv;
+                        const int gi = in ? (y0 + yl) * nx + x0 + cc : y0 * nx + x0;
+                        v[i] = make_cpx(a1[gi], a2[gi]);
+                        if (!in) v[i] = make_cpx((T)0, (T)0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < U; ++i) buf[threadIdx.x + (i0 + i) * NT] = v[i];
                 }
             }
         } else if (ROTATE) {
@@ -641,8 +650,8 @@ static hipError_t cols_inv_w(const KsArgs<T>& a) {
 // hold 32 or 64 values and run one or two; the four-step kernels need one
 // exchange less and give the forward pass 16-column strips (128-byte row
 // segments) up to 2048 points.  Measured (us, four-step / three-step, float):
-//   row pass:      512^2: 11.6 / 9.3, x 128: 100 / 107; 1024^2 x 128: 374 / 341;
-//                  2048^2 x 32: 614 / 431
+//   row pass:      512^2: 11.6 / 7.1; 1024^2 x 128: 374 / 341; 2048^2 x 32:
+//                  614 / 431
 //   inverse pass:  1024^2 x 128: 222 / 248; 2048^2 x 32: 303 / 257;
 //                  4096^2 x 8: 672 / 360
 //   forward pass:  rotating, 1024^2 x 128: 315 / 400; 2048^2 x 32: 430 / 488;
@@ -655,6 +664,14 @@ template <typename T, int LOGN, bool CROP>
 constexpr bool fwd3_always() { return sizeof(T) == 8 ? LOGN >= 10 : CROP && LOGN >= 11; }
 template <typename T, int LOGN>
 constexpr bool rows3() { return LOGN >= 9; }
+// Row passes of 128 and 256 points with few rows, where a launch takes as
+// long as one unit: a three-step unit spreads over twice the lanes.  All KS
+// passes of one map (us, four-step / three-step): 128^2 float 12.5 / 11.4,
+// 256^2 double 14.6 / 13.4, with kappa_B, whose inverse runs beside kappa_E's,
+// 16.3 / 13.7.  32 realisations of 256^2 take as long either way, 200 take 165
+// / 177 us of noise passes (128^2: 86 / 92), so the line is 4096 units.
+template <int LOGN>
+constexpr bool rows3_small() { return LOGN == 7 || LOGN == 8; }
 template <typename T, int LOGN>
 constexpr bool inv3() { return LOGN >= (sizeof(T) == 8 ? 10 : 11); }
 
@@ -683,6 +700,9 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
 
 template <typename T, int LOGN, bool CROP>
 static hipError_t ks_rows(const KsArgs<T>& a) {
+    if constexpr (rows3_small<LOGN>()) {
+        if (a.kB || ((long long)a.batch << (LOGN - 1)) <= 4096) return launch_ks3_rows<T, LOGN, CROP>(a);
+    }
     if constexpr (rows3<T, LOGN>()) {
         return launch_ks3_rows<T, LOGN, CROP>(a);
     } else {
@@ -690,12 +710,15 @@ static hipError_t ks_rows(const KsArgs<T>& a) {
         using RP = RowHalf<T, LOGN>;
         const int nx = CROP ? a.nx : N;
         const dim3 g((N / 2) / RP::UNITS, a.batch);
-        if (a.kB)
-            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                        k_ks_rows_half<T, LOGN, true, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
-        else
-            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                        k_ks_rows_half<T, LOGN, false, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+        if constexpr (!rows3_small<LOGN>()) {
+            if (a.kB) {
+                AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                            k_ks_rows_half<T, LOGN, true, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+                return hipGetLastError();
+            }
+        }
+        AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                    k_ks_rows_half<T, LOGN, false, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
         return hipGetLastError();
     }
 }
