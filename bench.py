@@ -75,8 +75,9 @@ def kernel_model(name, n, J, batch_real, stage_starts=()):
     credited work with half of the inverse arithmetic.
 
     bytes: the kernel's design hand-offs, each operand read or written once
-    per launch (the shared shear map once per launch; the double-precision
-    noise accumulators read and written once per launch).  ``stage_starts``
+    per launch (the shared shear map once per launch; each batch's running
+    mean and squared deviation, float32, written by the stages and read by
+    the finalize kernel).  ``stage_starts``
     lists the first scale of each noise stage (from the kernel names), which
     fixes how many scales a stage covers.  The signal's kernels
     (ks_cols_fwd, ks_rows, ks_cols_inv, starlet_stage_*) take one map; the
@@ -100,16 +101,16 @@ def kernel_model(name, n, J, batch_real, stage_starts=()):
         # read the packed spectrum, write the real map
         "ks_cols_inv": (8.0 * n2, fft1d),
         "ks_cols_inv_noise": (8.0 * n2 * B, B * fft1d),
-        "noise_finalize": ((16.0 + 12.0) * (J - 1) * n2, 3.0 * (J - 1) * n2),
+        "noise_finalize": ((8.0 * -(-R_REAL // B) + 12.0) * (J - 1) * n2, 3.0 * (J - 1) * n2),
         "count_peaks": (4.0 * (J - 1) * n2, 9.0 * (J - 1) * n2),
     }
     starts = sorted(stage_starts)
     for i, j0 in enumerate(starts):
         last = i + 1 == len(starts)
         ns = (J - j0) if last else starts[i + 1] - j0
-        # read c_{j0-1}, write c_{j0+ns-1} unless last, M and M2 of ns scales
-        rd = 4.0 * B * n2 + 16.0 * ns * n2
-        wr = (0.0 if last else 4.0 * B * n2) + 16.0 * ns * n2
+        # read c_{j0-1}, write c_{j0+ns-1} unless last and ns scales' statistics
+        rd = 4.0 * B * n2
+        wr = (0.0 if last else 4.0 * B * n2) + 8.0 * ns * n2
         models["noise_stage_j%d" % j0] = (rd + wr, ns * (19.0 + 4.0) * n2 * B)
         # the signal's write-mode stage: read c, write ns planes and the last c
         models["starlet_stage_j%d" % j0] = ((4.0 + 4.0 * ns + 4.0) * n2, ns * 19.0 * n2)

@@ -9,8 +9,9 @@
 // the paper leaves edges open, so the rule is the caller's: periodic (index
 // mod n), mirror (whole-sample symmetric: reflection about the first and
 // last samples, period 2(n-1)) or zero outside the field, applied to
-// c_{j-1} on each axis at every step.  One thread per output pixel; the
-// taps of interior pixels are contiguous rows, so the loads coalesce.
+// c_{j-1} on each axis at every step.  A step runs as LDS tiles up to a
+// dilation of bc_max_d, beyond it as a row and a column pass with one thread
+// per output pixel.
 #include <hip/hip_runtime.h>
 
 #include "amap_device.h"

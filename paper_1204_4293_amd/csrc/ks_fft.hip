@@ -25,8 +25,8 @@
 // LDS exchange separates the two steps.  Along x a transform's N2 threads
 // sit in one wavefront, so the exchange needs no workgroup barrier, and the
 // inverse transform starts from the forward output exactly as each thread
-// holds it.  Transforms whose per-thread DFTs would fill the register file
-// run the three-step kernels of ks_fft3.hip.
+// holds it.  Transforms whose per-thread DFTs would fill the register file,
+// and row passes of few rows, run the three-step kernels of ks_fft3.hip.
 #include "ks_device.h"
 
 namespace amap {

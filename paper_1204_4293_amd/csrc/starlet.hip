@@ -18,16 +18,17 @@
 // bounded halo overhead; scales whose dilation leaves no such tile use
 // per-scale row and column kernels.
 //
-// Noise statistics have two more stage kinds, for the coarse scales: tile
-// stages on the periodic sub-grid images of d0 (from scale j0 every tap
-// joins pixels congruent mod d0, so each sub-grid is a map of its own with
-// the dilations of a first stage), and a final stage on whole sub-grids
-// held in LDS.
+// Two more stage kinds serve the coarse scales.  From scale j0 every tap joins
+// pixels congruent mod d0, so each sub-grid is a periodic map of its own with
+// the dilations of a first stage: a final stage holds whole sub-grids in LDS
+// (for signals as strips of adjacent ones), and noise statistics also have
+// tile stages on the sub-grids as images.
 //
 // Maps (or noise realisations) are spread over gridDim.y.  For noise maps the
 // stages keep a running mean and sum of squared deviations per pixel
 // (Welford's update over the batch, then Chan, Golub & LeVeque's pairwise
-// merge in double precision), so no sum of squares of raw values is ever
+// merge in double precision, of all batches at the end where their partials
+// fit the workspace), so no sum of squares of raw values is ever
 // formed: with few realisations a pixel's spread can be far below its mean,
 // and S2 - S1^2 / n would then lose most of its digits.
 #include <type_traits>
