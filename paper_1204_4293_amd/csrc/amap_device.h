@@ -39,14 +39,13 @@ template <typename T>
 __host__ __device__ __forceinline__ cpx<T> operator+(cpx<T> a, cpx<T> b) { return make_cpx(a.x + b.x, a.y + b.y); }
 template <typename T>
 __host__ __device__ __forceinline__ cpx<T> operator-(cpx<T> a, cpx<T> b) { return make_cpx(a.x - b.x, a.y - b.y); }
+// Products that are summed are written as fused multiply-adds where the
+// compiler would choose which of the two to fuse: its choice may differ from
+// one kernel instantiation to the next, and results would then depend on how
+// a launch spreads its work.
 template <typename T>
 __host__ __device__ __forceinline__ cpx<T> cmul(cpx<T> a, cpx<T> b) {
-    return make_cpx(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// multiply by the conjugate of b
-template <typename T>
-__host__ __device__ __forceinline__ cpx<T> cmulc(cpx<T> a, cpx<T> b) {
-    return make_cpx(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+    return make_cpx((T)fma(a.x, b.x, -(a.y * b.y)), (T)fma(a.x, b.y, a.y * b.x));
 }
 // multiply by -i (forward) or +i (inverse)
 template <typename T, bool INV>
@@ -126,16 +125,16 @@ __device__ __forceinline__ void sincos_turn24(uint32_t w, float& sn, float& cs) 
 __device__ __forceinline__ void rotate_by_u32(uint32_t v, float& a, float& b) {
     float s, c;
     sincos_turn24(v >> 8, s, c);
-    const float na = a * c - b * s;
-    const float nb = a * s + b * c;
+    const float na = fma(a, c, -(b * s));
+    const float nb = fma(a, s, b * c);
     a = na; b = nb;
 }
 __device__ __forceinline__ void rotate_by_u32(uint32_t v, double& a, double& b) {
     const double u2 = (double)(v >> 8) * (1.0 / 8388608.0);
     double s, c;
     sincospi(u2, &s, &c);
-    const double na = a * c - b * s;
-    const double nb = a * s + b * c;
+    const double na = fma(a, c, -(b * s));
+    const double nb = fma(a, s, b * c);
     a = na; b = nb;
 }
 

@@ -26,7 +26,7 @@
 // sit in one wavefront, so the exchange needs no workgroup barrier, and the
 // inverse transform starts from the forward output exactly as each thread
 // holds it.  Transforms whose per-thread DFTs would fill the register file,
-// and row passes of few rows, run the three-step kernels of ks_fft3.hip.
+// and row passes from 128 points, run the three-step kernels of ks_fft3.hip.
 #include "ks_device.h"
 
 namespace amap {
@@ -294,7 +294,7 @@ __device__ __forceinline__ void ks_multiply(cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::
             const T dr = (m1sq - m2sq) * s;
             const T di = (c == N / 2 && t == 0) ? (T)0 : (m1 * two_m2) * s;
             const cpx<T> v = b[r][k2];
-            b[r][k2] = make_cpx(v.x * dr + v.y * di, v.y * dr - v.x * di);
+            b[r][k2] = cmul(v, make_cpx(dr, -di));
         }
     }
 }
@@ -421,7 +421,7 @@ __device__ __forceinline__ void ks_multiply_pair(cpx<T> (&b)[FS<LOGN>::RR][FS<LO
     // so its m1 is t - n/2 + c
     const T tb = (T)t - (hi ? (T)(N / 2) : (T)0);
     const auto apply = [](cpx<T>& v, T dr, T di) {
-        v = make_cpx(v.x * dr + v.y * di, v.y * dr - v.x * di);
+        v = cmul(v, make_cpx(dr, -di));
     };
 #pragma unroll
     for (int r = 0; r < RR; ++r) {
@@ -645,33 +645,32 @@ static hipError_t cols_inv_w(const KsArgs<T>& a) {
     return hipGetLastError();
 }
 
-// Which passes of a size run the three-step kernels.  Their 16 values per
-// thread leave room for four wavefronts per SIMD where the four-step kernels
-// hold 32 or 64 values and run one or two; the four-step kernels need one
-// exchange less and give the forward pass 16-column strips (128-byte row
-// segments) up to 2048 points.  Measured (us, four-step / three-step, float):
+// Which passes run the three-step kernels: by size, type, cropping and
+// rotation, never by the number of maps, since the two kinds of transform
+// round differently and a map's values may not depend on which maps share
+// its launch.  Their 16 values per thread leave room for four wavefronts per
+// SIMD where the four-step kernels hold 32 or 64 values and run one or two;
+// the four-step kernels need one exchange less and give the forward pass
+// 16-column strips (128-byte row segments) up to 2048 points.  Measured (us,
+// four-step / three-step, float):
 //   row pass:      512^2: 11.6 / 7.1; 1024^2 x 128: 374 / 341; 2048^2 x 32:
-//                  614 / 431
+//                  614 / 431; 128^2 x 200: 16.1 / 16.4; 256^2 x 200: 35 / 44,
+//                  but all passes of one map, whose row pass takes as long as
+//                  one unit: 128^2 12.5 / 11.4, 256^2 double 14.6 / 13.4, with
+//                  kappa_B, whose inverse runs beside kappa_E's, 16.3 / 13.7
 //   inverse pass:  1024^2 x 128: 222 / 248; 2048^2 x 32: 303 / 257;
 //                  4096^2 x 8: 672 / 360
 //   forward pass:  rotating, 1024^2 x 128: 315 / 400; 2048^2 x 32: 430 / 488;
 //                  4096^2 x 8: 998 / 816
-//                  one map of 2048^2: 41 / 22, five: 90 / 113; one of 4096^2: 112 / 129
+//                  2048^2, one map: 41 / 21, two: 46 / 43, four: 83 / 86, eight:
+//                  187 / 190; one of 4096^2: 112 / 129
 //                  rotating, 1000 x 1000 in 2048^2 x 15: 154 / 131
 // Double precision from 1024 points (whose per-thread DFTs would not fit the
 // registers) has three-step kernels only.
 template <typename T, int LOGN, bool CROP>
 constexpr bool fwd3_always() { return sizeof(T) == 8 ? LOGN >= 10 : CROP && LOGN >= 11; }
 template <typename T, int LOGN>
-constexpr bool rows3() { return LOGN >= 9; }
-// Row passes of 128 and 256 points with few rows, where a launch takes as
-// long as one unit: a three-step unit spreads over twice the lanes.  All KS
-// passes of one map (us, four-step / three-step): 128^2 float 12.5 / 11.4,
-// 256^2 double 14.6 / 13.4, with kappa_B, whose inverse runs beside kappa_E's,
-// 16.3 / 13.7.  32 realisations of 256^2 take as long either way, 200 take 165
-// / 177 us of noise passes (128^2: 86 / 92), so the line is 4096 units.
-template <int LOGN>
-constexpr bool rows3_small() { return LOGN == 7 || LOGN == 8; }
+constexpr bool rows3() { return LOGN >= 7; }
 template <typename T, int LOGN>
 constexpr bool inv3() { return LOGN >= (sizeof(T) == 8 ? 10 : 11); }
 
@@ -683,8 +682,8 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
         if constexpr (LOGN == 12) {
             if (a.rotate) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
-        if constexpr (LOGN == 11) {  // until 16-column strips fill the chip
-            if (!a.rotate && (1 << LOGN) / 16 * a.batch < 512) return launch_ks3_fwd<T, LOGN, CROP>(a);
+        if constexpr (LOGN == 11) {
+            if (!a.rotate) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
         constexpr int N = 1 << LOGN, WF = StripF<T, LOGN>::W;
         const int w = strip_width(N, CROP ? a.nx : N, a.batch, WF, a.rotate);
@@ -700,9 +699,6 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
 
 template <typename T, int LOGN, bool CROP>
 static hipError_t ks_rows(const KsArgs<T>& a) {
-    if constexpr (rows3_small<LOGN>()) {
-        if (a.kB || ((long long)a.batch << (LOGN - 1)) <= 4096) return launch_ks3_rows<T, LOGN, CROP>(a);
-    }
     if constexpr (rows3<T, LOGN>()) {
         return launch_ks3_rows<T, LOGN, CROP>(a);
     } else {
@@ -710,15 +706,12 @@ static hipError_t ks_rows(const KsArgs<T>& a) {
         using RP = RowHalf<T, LOGN>;
         const int nx = CROP ? a.nx : N;
         const dim3 g((N / 2) / RP::UNITS, a.batch);
-        if constexpr (!rows3_small<LOGN>()) {
-            if (a.kB) {
-                AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                            k_ks_rows_half<T, LOGN, true, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
-                return hipGetLastError();
-            }
-        }
-        AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                    k_ks_rows_half<T, LOGN, false, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+        if (a.kB)
+            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                        k_ks_rows_half<T, LOGN, true, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
+        else
+            AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
+                        k_ks_rows_half<T, LOGN, false, CROP><<<g, RP::NT, 0, a.stream>>>(a.C, a.tw, nx));
         return hipGetLastError();
     }
 }

@@ -254,27 +254,37 @@ k3_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_stri
 }
 
 // ---- P2 ---------------------------------------------------------------------------
-// One unit (spectral rows y and -y, or 0 and n/2) per workgroup of 2 L
-// threads: half i of them transforms its row and multiplies it by conj(D);
+// A unit (spectral rows y and -y, or 0 and n/2) takes 2 L threads, one unit
+// per workgroup or as many as fill a wavefront: half i of the threads
+// transforms its row and multiplies it by conj(D);
 // half 0 then forms kappa_E's Hermitian row y from the two (row -y mirrored)
 // and transforms it back, while half 1's wavefronts only keep the barriers
 // company, or, with WANT_B, do the same for kappa_B's row -y.  (Both rows in
 // one thread's registers spilled 300 to 900 bytes a lane.)  Built for four
 // wavefronts per SIMD in single precision, which costs a few spilled values
 // and is worth them (4096^2 x 8: 454 us, 714 at three wavefronts).
+template <int LOGN, int RX>
+struct Rows3 {
+    static constexpr int L = F3<LOGN, RX>::L;
+    static constexpr int UNITS = 2 * L < 64 ? 64 / (2 * L) : 1;
+    static constexpr int NT = UNITS * 2 * L;
+    // a row's exchange buffer, padded so that the rows of a wavefront fall on different banks
+    static constexpr int ELEMS = F3<LOGN, RX>::elems(1) + (L < 64 ? L : 0);
+};
 template <typename T, int LOGN, int RX, bool WANT_B, bool CROP>
-__global__ void __launch_bounds__((2 * F3<LOGN, RX>::L), (sizeof(T) == 4 ? 4 : 2))
+__global__ void __launch_bounds__((Rows3<LOGN, RX>::NT), (sizeof(T) == 4 ? 4 : 2))
 k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
-    using F = F3<LOGN, RX>;
-    constexpr int N = F::N, L = F::L, ELEMS = F::elems(1);
-    constexpr bool WAVE = L <= 64;  // a row's threads lie in one wavefront
-    __shared__ T buf[2 * ELEMS];
-    int half = (int)threadIdx.x / L;  // uniform in a wavefront unless a row takes half of one
+    using S = Rows3<LOGN, RX>;
+    constexpr int N = 1 << LOGN, L = S::L, ELEMS = S::ELEMS;
+    constexpr bool WAVE = L <= 64;       // a row's threads lie in one wavefront
+    constexpr bool UNIT = 2 * L <= 64;   // and so do a unit's
+    __shared__ T buf[S::UNITS * 2 * ELEMS];
+    int half = (int)threadIdx.x / L % 2;  // uniform in a wavefront unless a row takes part of one
     if constexpr (L >= 64) half = __builtin_amdgcn_readfirstlane(half);
-    const int t = threadIdx.x % L, q = blockIdx.x;
+    const int t = threadIdx.x % L, q = blockIdx.x * S::UNITS + (int)threadIdx.x / (2 * L);
     const int r0 = q, r1 = q == 0 ? N / 2 : N - q;
-    T* mine = buf + half * ELEMS;
-    const T* other = buf + (1 - half) * ELEMS;
+    T* mine = buf + ((int)threadIdx.x / (2 * L) * 2 + half) * ELEMS;
+    const T* other = buf + ((int)threadIdx.x / (2 * L) * 2 + 1 - half) * ELEMS;
     cpx<T>* map = C + (long long)blockIdx.y * N * N;
     cpx<T> a[1][RX];
     {
@@ -298,7 +308,7 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
             const T dr = (m1sq - m2sq) * s;
             const T di = (m == RX / 2 && t == 0) ? (T)0 : (m1 * two_m2) * s;
             const cpx<T> v = a[0][m];
-            a[0][m] = make_cpx(v.x * dr + v.y * di, v.y * dr - v.x * di);
+            a[0][m] = cmul(v, make_cpx(dr, -di));
         }
     }
     // H of this half's mode from its own K(k) and the mirrored K(-k), which
@@ -307,10 +317,10 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
     if (q != 0) {
 #pragma unroll
         for (int part = 0; part < 2; ++part) {  // one component at a time, in place
-            __syncthreads();
+            f3_sync<UNIT>();
 #pragma unroll
             for (int m = 0; m < RX; ++m) mine[t + L * m] = part ? a[0][m].y : a[0][m].x;
-            __syncthreads();
+            f3_sync<UNIT>();
             if (b_mode && !WANT_B) continue;
 #pragma unroll
             for (int m = 0; m < RX; ++m) {
@@ -329,10 +339,10 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
         cpx<T> v[RX];
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
-            __syncthreads();
+            f3_sync<UNIT>();
 #pragma unroll
             for (int m = 0; m < RX; ++m) mine[t + L * m] = part ? a[0][m].y : a[0][m].x;
-            __syncthreads();
+            f3_sync<UNIT>();
 #pragma unroll
             for (int m = 0; m < RX; ++m) {
                 const T w = mine[(N - t - L * m) & (N - 1)];
@@ -348,10 +358,10 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
         }
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
-            __syncthreads();
+            f3_sync<UNIT>();
 #pragma unroll
             for (int m = 0; m < RX; ++m) mine[t + L * m] = part ? v[m].y : v[m].x;
-            __syncthreads();
+            f3_sync<UNIT>();
 #pragma unroll
             for (int m = 0; m < RX; ++m) {
                 const T w = other[t + L * m];
@@ -365,7 +375,7 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
             a[0][m] = make_cpx(h0.x - h1.y, h0.y + h1.x);
         }
     }
-    if constexpr (WAVE) __syncthreads();  // the other half's reads are done (else the transform's barriers tell)
+    if constexpr (WAVE) f3_sync<UNIT>();  // the other half's reads are done (else the transform's barriers tell)
     if (!WANT_B && half != 0) {
         // the barriers of the other half's transform
         if constexpr (!WAVE) {
@@ -426,6 +436,10 @@ k3_cols_inv(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ kB
 }
 
 // ---- host launchers ----------------------------------------------------------------
+// Sizes whose rotating forward pass runs in four steps (ks_fft.hip).
+template <typename T, int LOGN, bool CROP>
+constexpr bool fwd3_plain() { return sizeof(T) == 4 && LOGN == 11 && !CROP; }
+
 template <typename T, int LOGN, bool CROP, int W, int IT>
 static hipError_t fwd3(const KsArgs<T>& a) {
     constexpr int N = 1 << LOGN;
@@ -435,15 +449,19 @@ static hipError_t fwd3(const KsArgs<T>& a) {
     // realisations of one input: all of a strip's on one XCD (4096^2 float, 8
     // realisations: 816 us, 1129 strip by strip)
     const bool shared_in = a.g_stride == 0 && !a.g1_off && a.batch > 1;
-    const int xcd = shared_in ? 2 : 1;
-    if (a.rotate)
-        AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
-                    k3_cols_fwd<T, LOGN, W, IT, true, CROP><<<g, S::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
-    else
-        AMAP_LAUNCH("ks_cols_fwd", a.stream,
-                    k3_cols_fwd<T, LOGN, W, IT, false, CROP><<<g, S::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
+    const int xcd = shared_in ? 2 : W <= 8 ? 1 : 0;
+    if constexpr (!fwd3_plain<T, LOGN, CROP>()) {
+        if (a.rotate) {
+            AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
+                        k3_cols_fwd<T, LOGN, W, IT, true, CROP><<<g, S::NT, 0, a.stream>>>(
+                            a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
+            return hipGetLastError();
+        }
+    }
+    if (a.rotate) return hipErrorInvalidValue;
+    AMAP_LAUNCH("ks_cols_fwd", a.stream,
+                k3_cols_fwd<T, LOGN, W, IT, false, CROP><<<g, S::NT, 0, a.stream>>>(
+                    a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
     return hipGetLastError();
 }
 
@@ -465,11 +483,16 @@ static hipError_t inv3(const KsArgs<T>& a) {
 // 4096^2 x 8: 816 / 2267; double 1024^2 x 16: 110 / 137, one map 18.1 / 14.8;
 // double 2048^2 x 8: 340 / 418, one map 36 / 42.  Two items per thread in
 // single precision, one where the launch is small (2048^2, one map: 20.4
-// against 22.1).
+// against 22.1).  Maps of 2048^2 floats take sixteen columns, four items per
+// thread, from one workgroup per CU on (us, 8 / 16 columns: one map 21 / 30,
+// two 60 / 43, three 81 / 78, four 110 / 86, eight 217 / 190).  None of this
+// changes a map's values: strips and items only spread the same transforms.
 template <typename T, int LOGN, bool CROP>
 hipError_t launch_ks3_fwd(const KsArgs<T>& a) {
     const long long wgs = ((CROP ? a.nx : 1 << LOGN) + 7) / 8 * (long long)a.batch;
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (fwd3_plain<T, LOGN, CROP>()) {
+        return wgs < 512 ? fwd3<T, LOGN, CROP, 8, 1>(a) : fwd3<T, LOGN, CROP, 16, 4>(a);
+    } else if constexpr (sizeof(T) == 4) {
         if constexpr (LOGN < 12) {
             if (wgs <= 512) return fwd3<T, LOGN, CROP, 8, 1>(a);
         }
@@ -485,17 +508,20 @@ hipError_t launch_ks3_fwd(const KsArgs<T>& a) {
 // Eight values per thread up to 512 points: twice the lanes of sixteen, half
 // the work of each (512^2, all KS passes, us, 16 / 8 values: float 19.0 / 16.8,
 // double 23.0 / 20.6; 200 realisations' noise passes 721 / 707, 1409 / 1378).
+// Rows of 128 points take two units per wavefront (200 maps: 16.4 us, 23.1 with
+// one unit of 32 threads per workgroup).
 template <typename T, int LOGN, bool CROP>
 hipError_t launch_ks3_rows(const KsArgs<T>& a) {
     constexpr int N = 1 << LOGN, RX = LOGN <= 9 ? 8 : 16;
+    using S = Rows3<LOGN, RX>;
     const int nx = CROP ? a.nx : N;
-    const dim3 g(N / 2, a.batch);
+    const dim3 g(N / 2 / S::UNITS, a.batch);
     if (a.kB)
         AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                    k3_rows<T, LOGN, RX, true, CROP><<<g, 2 * F3<LOGN, RX>::L, 0, a.stream>>>(a.C, a.tw, nx));
+                    k3_rows<T, LOGN, RX, true, CROP><<<g, S::NT, 0, a.stream>>>(a.C, a.tw, nx));
     else
         AMAP_LAUNCH(a.rotate ? "ks_rows_noise" : "ks_rows", a.stream,
-                    k3_rows<T, LOGN, RX, false, CROP><<<g, 2 * F3<LOGN, RX>::L, 0, a.stream>>>(a.C, a.tw, nx));
+                    k3_rows<T, LOGN, RX, false, CROP><<<g, S::NT, 0, a.stream>>>(a.C, a.tw, nx));
     return hipGetLastError();
 }
 
