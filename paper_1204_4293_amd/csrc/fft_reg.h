@@ -13,37 +13,23 @@ namespace amap {
 struct CS {
     double c, s;
 };
-constexpr double kPiD = 3.14159265358979323846264338327950288;
-constexpr double taylor_sin(double x) {
-    double t = x, s = x;
-    for (int i = 1; i < 30; ++i) { t *= -x * x / ((2 * i) * (2 * i + 1)); s += t; }
-    return s;
-}
-constexpr double taylor_cos(double x) {
-    double t = 1, s = 1;
-    for (int i = 1; i < 30; ++i) { t *= -x * x / ((2 * i - 1) * (2 * i)); s += t; }
-    return s;
-}
-// cos and sin of 2 pi k / R: octant reduction to [0, pi/4) and Taylor series;
-// exact on the axes.
+// cos and sin of 2 pi k / 64 for the first eighth of a turn, rounded to
+// double precision (17 digits determine the value).
+constexpr double kCos64[9] = {1.0, 0.9951847266721969, 0.9807852804032304, 0.9569403357322088, 0.9238795325112867,
+                              0.881921264348355, 0.8314696123025452, 0.773010453362737, 0.7071067811865476};
+constexpr double kSin64[9] = {0.0, 0.0980171403295606, 0.19509032201612828, 0.2902846772544624, 0.3826834323650898,
+                              0.47139673682599764, 0.5555702330196022, 0.6343932841636455, 0.7071067811865476};
+// cos and sin of 2 pi k / R, R a power of two up to 64: the angle mod a
+// quarter turn, reflected into its first half, then the quarter's signs, so
+// that every value is a correctly rounded one.
 constexpr CS cos_sin_2pi(int k, int R) {
-    k = ((k % R) + R) % R;
-    const long long k8 = 8LL * k;
-    const int oct = (int)(k8 / R);
-    const long long rem = k8 - (long long)oct * R;
-    const double x = (kPiD / 4) * (double)rem / (double)R;
-    double sx = taylor_sin(x), cx = taylor_cos(x);
-    if (rem == 0) { sx = 0; cx = 1; }
-    const double r2 = 0.70710678118654752440084436210484903928;
-    switch (oct) {
-        case 0: return CS{cx, sx};
-        case 1: return CS{r2 * (cx - sx), r2 * (cx + sx)};
-        case 2: return CS{-sx, cx};
-        case 3: return CS{-r2 * (cx + sx), r2 * (cx - sx)};
-        case 4: return CS{-cx, -sx};
-        case 5: return CS{-r2 * (cx - sx), -r2 * (cx + sx)};
-        case 6: return CS{sx, -cx};
-        default: return CS{r2 * (cx + sx), -r2 * (cx - sx)};
+    const int k64 = (((k % R) + R) % R) * (64 / R), r = k64 % 16;
+    const double c = r <= 8 ? kCos64[r] : kSin64[16 - r], s = r <= 8 ? kSin64[r] : kCos64[16 - r];
+    switch (k64 / 16) {
+        case 0: return CS{c, s};
+        case 1: return CS{-s, c};
+        case 2: return CS{-c, -s};
+        default: return CS{s, -c};
     }
 }
 

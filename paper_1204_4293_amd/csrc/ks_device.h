@@ -35,6 +35,13 @@ __device__ __forceinline__ int signed_freq(int i, int n) { return i < n / 2 ? i 
 // division in double.
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double recip(double x) { return 1.0 / x; }
+// x / den with r = recip(den); in double precision corrected by the
+// remainder, so that it carries one rounding like a division.
+__device__ __forceinline__ float ratio(float x, float, float r) { return x * r; }
+__device__ __forceinline__ double ratio(double x, double den, double r) {
+    const double q = x * r;
+    return fma(fma(-q, den, x), r, q);
+}
 
 // exp(-+2 pi i e / N) from the table of N entries (kTwiddles: the tables of
 // 4096, 2048, ... points one after the other, so that a small transform's

@@ -290,9 +290,9 @@ __device__ __forceinline__ void ks_multiply(cpx<T> (&b)[FS<LOGN>::RR][FS<LOGN>::
             const int c = N2 * r + N1 * k2;
             const T m1 = tf + (T)(c < N / 2 ? c : c - N);
             const T m1sq = m1 * m1;
-            const T s = scale * recip(fmax(m1sq + m2sq, (T)1));
-            const T dr = (m1sq - m2sq) * s;
-            const T di = (c == N / 2 && t == 0) ? (T)0 : (m1 * two_m2) * s;
+            const T den = fmax(m1sq + m2sq, (T)1), q = recip(den);
+            const T dr = scale * ratio(m1sq - m2sq, den, q);
+            const T di = (c == N / 2 && t == 0) ? (T)0 : scale * ratio(m1 * two_m2, den, q);
             const cpx<T> v = b[r][k2];
             b[r][k2] = cmul(v, make_cpx(dr, -di));
         }
@@ -430,10 +430,10 @@ __device__ __forceinline__ void ks_multiply_pair(cpx<T> (&b)[FS<LOGN>::RR][FS<LO
             const int c = N2 * r + N1 * k2;
             const T m1 = tb + (T)c;
             const T m1sq = m1 * m1;
-            const T s = scale * recip(fmax(m1sq + m2sq, (T)1));
-            T dr_lo = (m1sq - m2sq) * s, dr_hi = dr_lo;
+            const T den = fmax(m1sq + m2sq, (T)1), q = recip(den);
+            T dr_lo = scale * ratio(m1sq - m2sq, den, q), dr_hi = dr_lo;
             // the Nyquist column n/2 is the high half's c = 0 at t = 0
-            const T v = (c == 0 && hi && t == 0) ? (T)0 : (m1 * two_m2) * s;
+            const T v = (c == 0 && hi && t == 0) ? (T)0 : scale * ratio(m1 * two_m2, den, q);
             T di_lo = v, di_hi = -v;
             half_swap<N2>(dr_lo, dr_hi, hi);
             half_swap<N2>(di_lo, di_hi, hi);
@@ -653,8 +653,8 @@ static hipError_t cols_inv_w(const KsArgs<T>& a) {
 // the four-step kernels need one exchange less and give the forward pass
 // 16-column strips (128-byte row segments) up to 2048 points.  Measured (us,
 // four-step / three-step, float):
-//   row pass:      512^2: 11.6 / 7.1; 1024^2 x 128: 374 / 341; 2048^2 x 32:
-//                  614 / 431; 128^2 x 200: 16.1 / 16.4; 256^2 x 200: 35 / 44,
+//   row pass:      512^2: 11.6 / 7.1; 1024^2 x 128: 374 / 323; 2048^2 x 32:
+//                  614 / 392; 128^2 x 200: 16.1 / 16.4; 256^2 x 200: 35 / 44,
 //                  but all passes of one map, whose row pass takes as long as
 //                  one unit: 128^2 12.5 / 11.4, 256^2 double 14.6 / 13.4, with
 //                  kappa_B, whose inverse runs beside kappa_E's, 16.3 / 13.7

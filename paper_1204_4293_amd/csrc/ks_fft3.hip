@@ -40,57 +40,47 @@ __device__ __forceinline__ void f3_sync() {
     else __syncthreads();
 }
 
-// Steps 1 and 2 of thread t's line: DFT and twiddle.  READ takes every
-// twiddle from the table (the lanes of a strip's columns share the read);
-// else each is a product of at most two (step 2: three) table values, of
-// which one read per step differs from lane to lane.  READ measured better for the
-// column passes in double precision (2048^2, batch of 8: inverse pass 161
-// against 213 us) and worse where lanes differ (row pass, 4096^2 float: 779
-// against 440 us) or arithmetic is cheap (float columns: 1 to 4%).
-template <typename T, int LOGN, bool INV, bool READ, int RX>
+// Steps 1 and 2 of thread t's line: DFT and twiddle.  A twiddle is a table
+// value or the product of two: 15 (16) reads, most of them different in every
+// lane, took the row pass of 4096^2 floats 779 us against 440, and cost the
+// float columns 1 to 4%.  Four reads a step differ from lane to lane; with
+// one (step 2: products of three) the row passes took as long or longer
+// (1024^2 x 128: 337 us, now 320; 2048^2 x 32: 409, now 393) and the errors of
+// kappa and sigma were 4 to 10% larger.
+template <typename T, int LOGN, bool INV, int RX>
 __device__ __forceinline__ void f3_step1(cpx<T> (&a)[RX], int t, const cpx<T>* __restrict__ tw) {
     constexpr int LOG2X = RX == 16 ? 8 : 6;  // of the RX^2 points of the first two steps
     const int n2 = t / F3<LOGN, RX>::R3;
     dft_reg<T, RX, INV>(a);
-    if constexpr (READ) {
+    cpx<T> v[4];  // powers 1, 2, 3
 #pragma unroll
-        for (int k1 = 1; k1 < RX; ++k1) a[k1] = cmul(a[k1], table_twiddle<T, LOG2X, INV>(tw, n2 * k1));
-    } else {
-        cpx<T> v[4];  // powers 1, 2, 3
+    for (int j = 1; j < 4; ++j) v[j] = table_twiddle<T, LOG2X, INV>(tw, n2 * j);
 #pragma unroll
-        for (int j = 1; j < 4; ++j) v[j] = table_twiddle<T, LOG2X, INV>(tw, n2 * j);
-#pragma unroll
-        for (int i = 0; i < RX / 4; ++i) {
-            cpx<T> base{};
-            if (i) {
-                base = table_twiddle<T, LOG2X, INV>(tw, n2 * 4 * i);
-                a[4 * i] = cmul(a[4 * i], base);
-            }
-#pragma unroll
-            for (int j = 1; j < 4; ++j) a[4 * i + j] = cmul(a[4 * i + j], i ? cmul(base, v[j]) : v[j]);
+    for (int i = 0; i < RX / 4; ++i) {
+        cpx<T> base{};
+        if (i) {
+            base = table_twiddle<T, LOG2X, INV>(tw, n2 * 4 * i);
+            a[4 * i] = cmul(a[4 * i], base);
         }
+#pragma unroll
+        for (int j = 1; j < 4; ++j) a[4 * i + j] = cmul(a[4 * i + j], i ? cmul(base, v[j]) : v[j]);
     }
 }
-template <typename T, int LOGN, bool INV, bool READ, int RX>
+template <typename T, int LOGN, bool INV, int RX>
 __device__ __forceinline__ void f3_step2(cpx<T> (&a)[RX], int t, const cpx<T>* __restrict__ tw) {
     constexpr int R3 = F3<LOGN, RX>::R3;
     const int k1 = t / R3, n3 = t % R3;
     dft_reg<T, RX, INV>(a);
-    if constexpr (READ) {
+    // W_N^(n3 (k1 + 4 RX i)) W_N^(RX n3 j), k2 = 4 i + j
+    cpx<T> v[4];
 #pragma unroll
-        for (int k2 = 0; k2 < RX; ++k2) a[k2] = cmul(a[k2], table_twiddle<T, LOGN, INV>(tw, n3 * (k1 + RX * k2)));
-    } else {  // W_N^(n3 k1) W_N^(4 RX n3 i) W_N^(RX n3 j), k2 = 4 i + j: only the first differs in every lane
-        cpx<T> v[4];
+    for (int j = 1; j < 4; ++j) v[j] = table_twiddle<T, LOGN, INV>(tw, RX * n3 * j);
 #pragma unroll
-        for (int j = 1; j < 4; ++j) v[j] = table_twiddle<T, LOGN, INV>(tw, RX * n3 * j);
-        const cpx<T> w0 = table_twiddle<T, LOGN, INV>(tw, n3 * k1);
+    for (int i = 0; i < RX / 4; ++i) {
+        const cpx<T> base = table_twiddle<T, LOGN, INV>(tw, n3 * (k1 + 4 * RX * i));
+        a[4 * i] = cmul(a[4 * i], base);
 #pragma unroll
-        for (int i = 0; i < RX / 4; ++i) {
-            const cpx<T> base = i ? cmul(w0, table_twiddle<T, LOGN, INV>(tw, 4 * RX * n3 * i)) : w0;
-            a[4 * i] = cmul(a[4 * i], base);
-#pragma unroll
-            for (int j = 1; j < 4; ++j) a[4 * i + j] = cmul(a[4 * i + j], cmul(base, v[j]));
-        }
+        for (int j = 1; j < 4; ++j) a[4 * i + j] = cmul(a[4 * i + j], cmul(base, v[j]));
     }
 }
 // Step 3: the S3 DFTs of length R3; a[s R3 + n3] in, a[m] at frequency
@@ -110,6 +100,123 @@ __device__ __forceinline__ void f3_step3(cpx<T> (&a)[RX]) {
     }
 #pragma unroll
     for (int m = 0; m < RX; ++m) a[m] = o[m];
+}
+
+// The three steps in double precision with RX = 16, as radix-4 passes whose
+// inputs are multiplied by table twiddles: pass p joins four transforms of
+// 4^p points.  Two passes make a step (the third of 8 points ends in radix
+// 2), so that no step needs twiddles after its DFT.  27 to 31 table values a
+// thread, none of them a product, and fewer multiplications than a DFT_16 of
+// radix-2 butterflies and its twiddles: kappa's rms error at 1024^2 (2048^2)
+// is 4.2e-16 (4.4e-16), 5.6e-16 (6.2e-16) with those, and the rotating forward
+// pass of 1024^2 x 16 (2048^2 x 8) takes 95 us (329), 114 (372) with those.
+template <typename T, bool INV>
+__device__ __forceinline__ void radix4(cpx<T>& a0, cpx<T>& a1, cpx<T>& a2, cpx<T>& a3) {
+    const cpx<T> s0 = a0 + a2, d0 = a0 - a2, s1 = a1 + a3, d1 = rot90<T, INV>(a1 - a3);
+    a0 = s0 + s1;
+    a1 = d0 + d1;
+    a2 = s0 - s1;
+    a3 = d0 - d1;
+}
+// DFT_16 as two radix-4 passes over a[j]: in, j = 4 u + v; out, k = q + 4 r.
+// w1(u) (u = 1..3) multiplies the inputs of the first pass, w2(v, q) (v =
+// 1..3) those of the second.
+template <typename T, bool INV, typename W1, typename W2>
+__device__ __forceinline__ void radix4_pair(cpx<T> (&a)[16], W1&& w1, W2&& w2) {
+#pragma unroll
+    for (int u = 1; u < 4; ++u) w1(u, a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) radix4<T, INV>(a[v], a[4 + v], a[8 + v], a[12 + v]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int v = 1; v < 4; ++v) w2(v, q, a[4 * q + v]);
+        radix4<T, INV>(a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]);
+    }
+    // a[4 q + r] holds k = q + 4 r
+    cpx<T> o[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) o[k] = a[4 * (k % 4) + k / 4];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a[k] = o[k];
+}
+struct W16Table {  // exp(-2 pi i k / 16)
+    double c[10], s[10];
+    constexpr W16Table() : c(), s() {
+        for (int k = 0; k < 10; ++k) {
+            const CS w = cos_sin_2pi(k, 16);
+            c[k] = w.c;
+            s[k] = -w.s;
+        }
+    }
+};
+template <typename T, bool INV>
+__device__ __forceinline__ void radix4_step1(cpx<T> (&a)[16]) {
+    constexpr W16Table w;
+    radix4_pair<T, INV>(
+        a, [](int, cpx<T>&, cpx<T>&, cpx<T>&, cpx<T>&) {},
+        [&](int v, int q, cpx<T>& x) {
+            if (v * q == 4) x = rot90<T, INV>(x);
+            else if (q != 0) x = cmul(x, make_cpx((T)w.c[v * q], (T)(INV ? -w.s[v * q] : w.s[v * q])));
+        });
+}
+template <typename T, int LOGN, bool INV>
+__device__ __forceinline__ void radix4_step2(cpx<T> (&a)[16], int t, const cpx<T>* __restrict__ tw) {
+    const int k1 = t / F3<LOGN>::R3;
+    radix4_pair<T, INV>(
+        a,
+        [&](int u, cpx<T>& x0, cpx<T>& x1, cpx<T>& x2, cpx<T>& x3) {
+            const cpx<T> w = table_twiddle<T, 6, INV>(tw, u * k1);
+            x0 = cmul(x0, w); x1 = cmul(x1, w); x2 = cmul(x2, w); x3 = cmul(x3, w);
+        },
+        [&](int v, int q, cpx<T>& x) { x = cmul(x, table_twiddle<T, 8, INV>(tw, v * (k1 + 16 * q))); });
+}
+// The S3 DFTs of length R3 of frequencies K = t + L s.
+template <typename T, int LOGN, bool INV>
+__device__ __forceinline__ void radix4_step3(cpx<T> (&a)[16], int t, const cpx<T>* __restrict__ tw) {
+    constexpr int R3 = F3<LOGN>::R3, S3 = F3<LOGN>::S3, L = F3<LOGN>::L;
+    if constexpr (R3 == 16) {
+        radix4_pair<T, INV>(
+            a,
+            [&](int u, cpx<T>& x0, cpx<T>& x1, cpx<T>& x2, cpx<T>& x3) {
+                const cpx<T> w = table_twiddle<T, LOGN - 2, INV>(tw, u * t);
+                x0 = cmul(x0, w); x1 = cmul(x1, w); x2 = cmul(x2, w); x3 = cmul(x3, w);
+            },
+            [&](int v, int q, cpx<T>& x) { x = cmul(x, table_twiddle<T, LOGN, INV>(tw, v * (t + 256 * q))); });
+    } else {
+        constexpr int V = R3 / 4;  // n3 = V u + v: a radix-4 pass over u, for V = 2 one of radix 2 over v
+        static_assert(V == 1 || V == 2, "third steps of 4, 8 or 16 points");
+        cpx<T> o[16];
+#pragma unroll
+        for (int s = 0; s < S3; ++s) {
+            const int K = t + L * s;
+            cpx<T> z[V][4];
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) z[v][u] = a[s * R3 + V * u + v];
+#pragma unroll
+            for (int u = 1; u < 4; ++u) {
+                const cpx<T> w = table_twiddle<T, LOGN - V + 1, INV>(tw, u * K);
+#pragma unroll
+                for (int v = 0; v < V; ++v) z[v][u] = cmul(z[v][u], w);
+            }
+#pragma unroll
+            for (int v = 0; v < V; ++v) radix4<T, INV>(z[v][0], z[v][1], z[v][2], z[v][3]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (V == 1) {
+                    o[s + S3 * q] = z[0][q];
+                } else {
+                    const cpx<T> y = cmul(z[1][q], table_twiddle<T, LOGN, INV>(tw, K + 256 * q));
+                    o[s + S3 * q] = z[0][q] + y;
+                    o[s + S3 * (q + 4)] = z[0][q] - y;
+                }
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 16; ++m) a[m] = o[m];
+    }
 }
 
 // Addresses of the two exchanges in a buffer of W interleaved lines (line
@@ -160,15 +267,24 @@ __device__ __forceinline__ void f3_exchange(cpx<T> (&a)[ITEMS][RX], T* buf, int 
 // The whole transform of the items a thread holds.
 template <typename T, int LOGN, int W, int ITEMS, bool INV, bool WAVE, int DT, int RX = 16>
 __device__ __forceinline__ void f3_transform(cpx<T> (&a)[ITEMS][RX], T* buf, int t0, const cpx<T>* __restrict__ tw) {
-    constexpr bool READ = W > 1 && sizeof(T) == 8;
+    constexpr bool R4 = sizeof(T) == 8 && RX == 16;
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) f3_step1<T, LOGN, INV, READ, RX>(a[i], t0 + i * DT, tw);
+    for (int i = 0; i < ITEMS; ++i) {
+        if constexpr (R4) radix4_step1<T, INV>(a[i]);
+        else f3_step1<T, LOGN, INV, RX>(a[i], t0 + i * DT, tw);
+    }
     f3_exchange<T, LOGN, W, ITEMS, false, WAVE, DT, RX>(a, buf, t0);
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) f3_step2<T, LOGN, INV, READ, RX>(a[i], t0 + i * DT, tw);
+    for (int i = 0; i < ITEMS; ++i) {
+        if constexpr (R4) radix4_step2<T, LOGN, INV>(a[i], t0 + i * DT, tw);
+        else f3_step2<T, LOGN, INV, RX>(a[i], t0 + i * DT, tw);
+    }
     f3_exchange<T, LOGN, W, ITEMS, true, WAVE, DT, RX>(a, buf, t0);
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) f3_step3<T, LOGN, INV, RX>(a[i]);
+    for (int i = 0; i < ITEMS; ++i) {
+        if constexpr (R4) radix4_step3<T, LOGN, INV>(a[i], t0 + i * DT, tw);
+        else f3_step3<T, LOGN, INV, RX>(a[i]);
+    }
 }
 
 // Column strips: W columns, ITEMS items of 16 values per thread.
@@ -262,7 +378,8 @@ k3_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_stri
 // company, or, with WANT_B, do the same for kappa_B's row -y.  (Both rows in
 // one thread's registers spilled 300 to 900 bytes a lane.)  Built for four
 // wavefronts per SIMD in single precision, which costs a few spilled values
-// and is worth them (4096^2 x 8: 454 us, 714 at three wavefronts).
+// and is worth them (4096^2 x 8: 420 us; 714 at three wavefronts, 454 at four,
+// with other twiddles).
 template <int LOGN, int RX>
 struct Rows3 {
     static constexpr int L = F3<LOGN, RX>::L;
@@ -304,9 +421,9 @@ k3_rows(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
         for (int m = 0; m < RX; ++m) {
             const T m1 = (T)t + (T)(m < RX / 2 ? L * m : L * m - N);
             const T m1sq = m1 * m1;
-            const T s = scale * recip(fmax(m1sq + m2sq, (T)1));
-            const T dr = (m1sq - m2sq) * s;
-            const T di = (m == RX / 2 && t == 0) ? (T)0 : (m1 * two_m2) * s;
+            const T den = fmax(m1sq + m2sq, (T)1), r = recip(den);
+            const T dr = scale * ratio(m1sq - m2sq, den, r);
+            const T di = (m == RX / 2 && t == 0) ? (T)0 : scale * ratio(m1 * two_m2, den, r);
             const cpx<T> v = a[0][m];
             a[0][m] = cmul(v, make_cpx(dr, -di));
         }
@@ -409,7 +526,8 @@ k3_cols_inv(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ kB
     int sx, b;
     strip_of(xcd, sx, b);
     const bool second = sx >= strips;  // kappa_B
-    const int c = threadIdx.x % W, t0 = threadIdx.x / W;
+    const int c = threadIdx.x % W;
+    int t0 = threadIdx.x / W;
     const int col = (second ? sx - strips : sx) * W + c;
     const cpx<T>* in = C + (long long)b * N * N + (second ? N / 2 : 0) + col;
     cpx<T> a[ITEMS][16];
@@ -418,6 +536,17 @@ k3_cols_inv(const cpx<T>* __restrict__ C, T* __restrict__ kE, T* __restrict__ kB
 #pragma unroll
         for (int m = 0; m < 16; ++m) a[i][m] = in[(long long)(t0 + i * DT + L * m) * N];
     f3_transform<T, LOGN, W, ITEMS, true, false, DT>(a, buf + c, t0, tw);
+    if constexpr (sizeof(T) == 8) {
+        // every value complete, and no address formed, before the first store:
+        // left free, the compiler moves the last butterflies into the stores'
+        // conditions and their addresses ahead of the loads, and spills (4096^2:
+        // 60 us, 104 so; a 2000 x 2000 field with kappa_B in 2048^2: 34, 62)
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+#pragma unroll
+            for (int m = 0; m < 16; ++m) asm volatile("" : "+v"(a[i][m].x), "+v"(a[i][m].y));
+        asm volatile("" : "+v"(t0));
+    }
     const int os = CROP ? nx : N;
     T* o = (second ? kB + (long long)b * out_stride
                    : kE + (kE_off ? kE_off[b] : (long long)b * out_stride)) + 2 * col;
@@ -480,8 +609,8 @@ static hipError_t inv3(const KsArgs<T>& a) {
 // Strips of eight columns keep the spectrum's row segments at 64 bytes (128 in
 // double precision); four-column strips only where eight would leave CUs
 // idle, or 4096 doubles would not fit.  Measured (us, 8 / 4 columns): float
-// 4096^2 x 8: 816 / 2267; double 1024^2 x 16: 110 / 137, one map 18.1 / 14.8;
-// double 2048^2 x 8: 340 / 418, one map 36 / 42.  Two items per thread in
+// 4096^2 x 8: 816 / 2267; double 1024^2 x 16: 95 / 145, one map 18.2 / 16.0;
+// double 2048^2 x 8: 329 / 409, one map 32 / 40.  Two items per thread in
 // single precision, one where the launch is small (2048^2, one map: 20.4
 // against 22.1).  Maps of 2048^2 floats take sixteen columns, four items per
 // thread, from one workgroup per CU on (us, 8 / 16 columns: one map 21 / 30,
@@ -527,8 +656,8 @@ hipError_t launch_ks3_rows(const KsArgs<T>& a) {
 
 // The packed columns are pairs, so a strip of four writes eight columns of
 // kappa.  Measured (us, 8 / 4 columns): float 4096^2 x 8: 400 / 360; float
-// 2048^2 x 32 (two items): 257 / -; double 1024^2 x 16: 75 / 71, one map
-// 13 / 10; double 2048^2 x 8: 167 / 161.
+// 2048^2 x 32 (two items): 257 / -; double, where one map counts for more than
+// many: 1024^2 11.4 / 9.7, x 16: 56 / 66; 2048^2 22.9 / 18.7, x 8: 131 / 136.
 template <typename T, int LOGN, bool CROP>
 hipError_t launch_ks3_inv(const KsArgs<T>& a) {
     if constexpr (sizeof(T) == 4 && LOGN < 12) return inv3<T, LOGN, CROP, 8, 2>(a);
