@@ -19,14 +19,15 @@
 // registers), leaves S and D in its own LDS rows and walks the taps in groups
 // of four dx: one new 4-vector of S and of D from LDS and the group's eight
 // weights from the scalar cache (dy is uniform across the wavefront) for
-// 8 P fused multiply-adds.  Taps outside the disc carry zero weight.  No
-// barrier: a wavefront reads only what it wrote.  SPLIT wavefronts of a
+// 8 P fused multiply-adds.  The first and last group of a row skip the taps
+// outside the disc (a zero weight would carry a NaN or an infinity there into
+// the sum).  No barrier: a wavefront reads only what it wrote.  SPLIT wavefronts of a
 // workgroup take the row offsets of one segment in turn and add up in a
 // fixed order at the end.  The kernel is bound by the multiply-adds: 1024^2,
-// cut 64, float in 423 us, i.e. 27 GFLOP done (half of the plain sum's 54) at
-// 64 TFLOP/s of the 78.6 that unpacked FP32 instructions reach.  A ring of
+// cut 64, float in 411 us, i.e. 27 GFLOP done (half of the plain sum's 54) at
+// 66 TFLOP/s of the 78.6 that unpacked FP32 instructions reach.  A ring of
 // input rows shared by the workgroup without the pairing of rows took 991 us,
-// and 292 us against 115 at cut 32; maps under 512 px, which had no staging,
+// and 292 us against 123 at cut 32; maps under 512 px, which had no staging,
 // took 1.8 ms at 256^2, cut 64, against 45 us.
 //
 // The weights are tabulated on the device in the same stream (a table built
@@ -96,12 +97,14 @@ __device__ __forceinline__ void st4(T* p, const Vec4<T>& r) {
 
 // The 4 x P taps of one group: dx = dx0 + q (q < 4) for outputs i < P, from
 // the windows v of S and u of D (P + 4 values from dx0 on); w holds the
-// group's four Q cos 2phi and four Q sin 2phi.
-template <typename T, int P>
-__device__ __forceinline__ void direct_group(T (&acc)[P], const T* __restrict__ w,
-                                             const Vec4<T> (&v)[P / 4 + 1], const Vec4<T> (&u)[P / 4 + 1]) {
+// group's four Q cos 2phi and four Q sin 2phi.  EDGE: only the taps lo <= q
+// <= hi (uniform across the wavefront), which lie inside the disc.
+template <typename T, int P, bool EDGE>
+__device__ __forceinline__ void direct_group(T (&acc)[P], const T* __restrict__ w, const Vec4<T> (&v)[P / 4 + 1],
+                                             const Vec4<T> (&u)[P / 4 + 1], int lo, int hi) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        if (EDGE && (q < lo || q > hi)) continue;
         const T wc = w[q], ws = w[4 + q];
 #pragma unroll
         for (int i = 0; i < P; ++i)
@@ -179,21 +182,29 @@ k_map_direct_rows(const T* __restrict__ g1, const T* __restrict__ g2, int logn, 
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
         if (dy + SPLIT <= R) prefetch(dy + SPLIT);
         const int h = half[dy];
+        if (h < 0) continue;
         const T* r1 = S + P * li + R4;
         const T* r2 = Dr + P * li + R4;
         const T* wrow = gtab + ((long long)dy * ng + R4 / 4) * 8;
-        const int gb = -((h + 3) >> 2), ge = h >> 2;  // groups dx0 = 4 g cover [-h, h]; none for h < 0
+        const int gb = -((h + 3) >> 2), ge = h >> 2;  // groups dx0 = 4 g cover [-h, h]
         // the window of group g is the PV + 1 4-vectors from 4 g on
         Vec4<T> v[PV + 1], u[PV + 1];
-        if (h >= 0) {
 #pragma unroll
-            for (int k = 0; k < PV; ++k) {
-                v[k] = ld4(r1 + 4 * (gb + k));
-                u[k] = ld4(r2 + 4 * (gb + k));
-            }
+        for (int k = 0; k < PV; ++k) {
+            v[k] = ld4(r1 + 4 * (gb + k));
+            u[k] = ld4(r2 + 4 * (gb + k));
         }
-        int g = h >= 0 ? gb : ge + 1;
-        for (; g + PV <= ge; g += PV + 1) {
+        // the first and the last group of the row may reach out of the disc
+        const auto edge = [&](int g) {
+            v[PV] = ld4(r1 + 4 * (g + PV));
+            u[PV] = ld4(r2 + 4 * (g + PV));
+            direct_group<T, P, true>(acc, wrow + g * 8, v, u, -h - 4 * g, h - 4 * g);
+#pragma unroll
+            for (int k = 0; k < PV; ++k) { v[k] = v[k + 1]; u[k] = u[k + 1]; }
+        };
+        edge(gb);
+        int g = gb + 1;
+        for (; g + PV < ge; g += PV + 1) {
             // PV + 1 groups per iteration: the window is renamed, not moved
 #pragma unroll
             for (int s = 0; s < PV + 1; ++s) {
@@ -205,16 +216,17 @@ k_map_direct_rows(const T* __restrict__ g1, const T* __restrict__ g2, int logn, 
                     vv[k] = v[(s + k) % (PV + 1)];
                     uu[k] = u[(s + k) % (PV + 1)];
                 }
-                direct_group<T, P>(acc, wrow + (g + s) * 8, vv, uu);
+                direct_group<T, P, false>(acc, wrow + (g + s) * 8, vv, uu, 0, 3);
             }
         }
-        for (; g <= ge; ++g) {
+        for (; g < ge; ++g) {
             v[PV] = ld4(r1 + 4 * (g + PV));
             u[PV] = ld4(r2 + 4 * (g + PV));
-            direct_group<T, P>(acc, wrow + g * 8, v, u);
+            direct_group<T, P, false>(acc, wrow + g * 8, v, u, 0, 3);
 #pragma unroll
             for (int k = 0; k < PV; ++k) { v[k] = v[k + 1]; u[k] = u[k + 1]; }
         }
+        if (gb < ge) edge(ge);
     }
     if constexpr (SPLIT > 1) {
         __syncthreads();  // every wavefront is done with its rows
