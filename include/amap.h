@@ -98,7 +98,8 @@ amap_status amap_sync(amap_ctx_t ctx, void* stream);
 size_t amap_workspace_bytes(amap_ctx_t ctx);
 
 /* Tile autotuning (on by default).  The first starlet transform of each
- * shape (element type, n, J, signal or noise statistics, batch) on a stream
+ * shape (element type, n, J, signal or noise statistics and how these are
+ * merged, batch) on a stream
  * that is not being captured times the candidate LDS tiles of every stage
  * start and scale count on the call's own buffers (for noise statistics
  * also stages on sub-grid images and final sub-grid stages) and keeps, per
@@ -116,7 +117,10 @@ amap_status amap_set_autotune(amap_ctx_t ctx, int enable);
 
 /* Writes the context's tuned schedules as JSON into buf (len bytes including
  * the NUL): [{"mode": 1 (tuned) | 2 (analytic with sub-grid final stage, see
- * amap_set_autotune), "elem": bytes per value, "logn", "J", "noise": 0|1, "batch",
+ * amap_set_autotune), "elem": bytes per value, "logn", "J", "noise": 0|1|2 (2:
+ * statistics of so many batches that they are merged batch by batch instead of
+ * at the end; a loaded entry with 1 serves these too unless there is one with
+ * 2), "batch",
  * "stages": [[j0, ns, tile width, tile sub-rows, realisations per LDS
  * pass, kind], ...]}, ...].  Every scale from j0 on couples only pixels
  * congruent mod d = 2^(j0-1) (the a-trous dilations, Sec. 2.3), so the d^2

@@ -10,6 +10,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -164,9 +165,11 @@ struct amap_ctx {
     cpx<double>* tw64 = nullptr;
     Workspace ws;
     EventTimer* timer = nullptr;
-    // tuned starlet schedules: (element size, log2 n, J, noise mode, batch) -> plan
-    // (nstages == 0: the analytic planner)
+    // tuned starlet schedules: (element size, log2 n, J, mode, batch) -> plan
+    // (nstages == 0: the analytic planner); mode 0: signal, 1: noise statistics
+    // merged at the end, 2: merged batch by batch
     mutable std::map<std::array<int, 5>, StagePlan> plans;
+    std::set<std::array<int, 5>> loaded;  // mode-1 shapes whose schedule was loaded: it serves mode 2 too
     int autotune = 1;  // 0 analytic, 1 tuned, 2 analytic with sub-grid final noise stages
     mutable std::map<std::array<int, 5>, StagePlan> plans_sub;  // mode 2 schedules
     int noise_cap = 0;  // > 0: at most this many noise realisations per launch sequence
@@ -174,13 +177,16 @@ struct amap_ctx {
 
 namespace {
 // The tuned schedule for a starlet launch shaped like `a`, tuning it on a's
-// buffers on first use (which overwrites a's outputs and, in noise mode, M
-// and M2: callers tune before they zero the statistics).  Never tunes while
-// the stream is being captured; then the analytic plan is used.
+// buffers on first use (which overwrites a's outputs and, in noise mode, the
+// statistics: callers tune before they write them).  Never tunes while the
+// stream is being captured; then the analytic plan is used.  Noise statistics
+// merged at the end and batch by batch are shapes of their own: their stages
+// end in other work (8 bytes stored a pixel and scale, or 32 read and
+// written), so one's schedule is not the other's, whichever ran first.
 template <typename T>
 const StagePlan* tuned_plan(const amap_ctx* c, const StarletArgs<T>& a) {
     if (c->autotune == 0) return nullptr;
-    const std::array<int, 5> key{(int)sizeof(T), a.logn, a.J, a.M != nullptr, a.batch};
+    std::array<int, 5> key{(int)sizeof(T), a.logn, a.J, a.M != nullptr, a.batch};
     if (c->autotune == 2) {
         if (!a.M) return nullptr;
         auto is = c->plans_sub.find(key);
@@ -189,6 +195,11 @@ const StagePlan* tuned_plan(const amap_ctx* c, const StarletArgs<T>& a) {
         analytic_subgrid_plan<T>(1 << a.logn, a.J, &p);
         StagePlan& kept = (c->plans_sub[key] = p);
         return kept.nstages ? &kept : nullptr;
+    }
+    if (a.M && !a.defer) {
+        const std::array<int, 5> at_end = key;
+        key[3] = 2;
+        if (!c->plans.count(key) && c->loaded.count(at_end)) key = at_end;
     }
     auto it = c->plans.find(key);
     if (it != c->plans.end()) return &it->second;
@@ -377,10 +388,15 @@ amap_status enqueue_noise(const amap_ctx* ctx, char* ws, int n, int J, const T* 
     t.planes = nullptr; t.planes_stride = 0; t.cbuf0 = cb0; t.cbuf1 = cb1; t.tmp = tmp;
     t.wbuf = wb; t.M = M; t.M2 = M2; t.part = defer ? tmp : part; t.stream = s; t.defer = defer;
     const StagePlan* plan = tuned_plan<T>(ctx, t);
-    const NoiseParts parts = defer ? noise_parts<T>(logn, J, B, plan) : NoiseParts();
+    NoiseParts parts = defer ? noise_parts<T>(logn, J, B, plan) : NoiseParts();
     bool deferred = parts.ok && (size_t)nbatch * parts.block * sizeof(T) <= room;
     for (int j = 0; deferred && j < J - 1; ++j)
         deferred = (long long)nbatch * parts.groups[j] <= kMaxMerge;
+    if (t.defer && !deferred) {
+        t.defer = false;
+        t.part = part;
+        plan = tuned_plan<T>(ctx, t);
+    }
     // M and M2 need no clearing: the first batch's merges write them unread
     for (int r0 = 0; r0 < n_real; r0 += B) {
         const int bb = (n_real - r0) < B ? (n_real - r0) : B;
@@ -575,7 +591,7 @@ amap_status amap_plans_load(amap_ctx_t c, const char* json) {
         p = st;
         const int elem = e.key[0], logn = e.key[1], J = e.key[2], noise = e.key[3], batch = e.key[4];
         if ((e.mode != 1 && e.mode != 2) || (elem != 4 && elem != 8) || logn < 4 || logn > kMaxLogN ||
-            J < 2 || (1 << J) > (1 << logn) || (noise != 0 && noise != 1) || batch < 1)
+            J < 2 || (1 << J) > (1 << logn) || noise < 0 || noise > (e.mode == 1 ? 2 : 1) || batch < 1)
             return fail(AMAP_E_INVAL, "schedule %d: bad mode, element size, size, J, noise flag or batch", idx);
         if (e.plan.nstages > 0) {
             const bool ok = elem == 4 ? plan_valid<float>(1 << logn, J, noise != 0, e.plan)
@@ -585,7 +601,10 @@ amap_status amap_plans_load(amap_ctx_t c, const char* json) {
         got.push_back(e);
         ++idx;
     }
-    for (const Entry& e : got) (e.mode == 1 ? c->plans : c->plans_sub)[e.key] = e.plan;
+    for (const Entry& e : got) {
+        (e.mode == 1 ? c->plans : c->plans_sub)[e.key] = e.plan;
+        if (e.mode == 1 && e.key[3] == 1) c->loaded.insert(e.key);
+    }
     return AMAP_OK;
 }
 

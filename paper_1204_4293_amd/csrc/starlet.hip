@@ -1983,7 +1983,10 @@ hipError_t tune_starlet(const StarletArgs<T>& a, int reps, StagePlan* out) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    // the average time of one stage alone (reps launches after a warm one)
+    // the average time of one stage alone (reps launches after a warm one);
+    // where its partials are merged at the end, with the time the finalize
+    // kernel takes to read them (3.6 bytes a picosecond: 4096^2, J = 9, four
+    // batches in 1.2 ms), which multiplies with the stage's groups
     auto time_stage = [&](const StagePlan::Stage& st, float* us, int cout_logd = 0) {
         StagePlan sub;
         sub.nstages = 1;
@@ -2003,6 +2006,12 @@ hipError_t tune_starlet(const StarletArgs<T>& a, int reps, StagePlan* out) {
         float ms = 0.f;
         if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);
         *us = 1e3f * ms / reps;
+        StageRun run[16];
+        int count = 0;
+        if (a.defer && r == hipSuccess) r = resolve_stages<T>(n, J, true, &sub, run, &count);
+        if (a.defer && r == hipSuccess)
+            *us += 1e-6f / 3.6f * noise_groups(noise_tiles(n, run[0]), a.batch) * st.ns * 2 *
+                   (float)(sizeof(T) << (2 * a.logn));
         if (r == hipSuccess && tune_log()) {
             const char* kind = st.kind == kStageSubgrid ? "sub-grids" : st.kind == kStageImages ? "image tile" : "tile";
             std::fprintf(stderr, "amap tune: n=%d J=%d %s batch=%d stage j0=%d ns=%d %s %dx%d rb=%d: %.1f us\n",
