@@ -189,7 +189,6 @@ template <typename T>
 hipError_t launch_noise_finalize_parts(int logn, int J, int R, int B, const NoiseParts& parts,
                                        const void* part, const T* planes_signal, T* sigma, T* snr,
                                        hipStream_t s, const StatLayout& layout);
-hipError_t launch_zero_f64(double* p, long long count, hipStream_t s);
 hipError_t launch_zero_i64(long long* p, long long count, hipStream_t s);
 
 template <typename T>

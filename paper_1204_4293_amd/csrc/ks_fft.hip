@@ -75,16 +75,12 @@ using StripF = Strip4<T, LOGN, true, WREQ>;
 template <typename T, int LOGN, int WREQ = 0>
 using StripI = Strip4<T, LOGN, false, WREQ>;
 
-template <typename T, int LOGN>
-struct Row4 {
-    static constexpr int N2 = FS<LOGN>::N2, N1 = FS<LOGN>::N1;
-    static constexpr int N = 1 << LOGN;
-    static constexpr int NT = 128;
-    static constexpr int LINES0 = NT / N2 > 0 ? NT / N2 : 1;
-    static constexpr int LINES = LINES0 > N ? N : LINES0;
-    // exchange region per line: forward [N1][N2+1], inverse [N2][N1+1]
-    static constexpr int EX = (N1 * (N2 + 1)) > (N2 * (N1 + 1)) ? (N1 * (N2 + 1)) : (N2 * (N1 + 1));
-};
+// Exchange region of one row: forward [N1][N2+1], inverse [N2][N1+1].
+template <int LOGN>
+constexpr int row4_elems() {
+    constexpr int N1 = FS<LOGN>::N1, N2 = FS<LOGN>::N2;
+    return (N1 * (N2 + 1)) > (N2 * (N1 + 1)) ? (N1 * (N2 + 1)) : (N2 * (N1 + 1));
+}
 
 // ---- P1: load shears (optionally rotate), forward FFT along y (four-step) -------
 // CROP: the shears are ny x nx, row-major, zero outside; only the strips they
@@ -170,14 +166,15 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
                     for (int i = 0; i < U; ++i) buf[threadIdx.x + (i0 + i) * NT] = v[i];
                 }
             }
-        } else if (ROTATE) {
+        } else if constexpr (ROTATE) {
             // one Philox block covers 8 consecutive pixels of a row
-            constexpr int OCT_PER_ROW = (W + 7) / 8;
+            static_assert(W % 8 == 0, "a segment is whole blocks");
+            constexpr int OCT_PER_ROW = W / 8;
             const uint64_t r = r0 + b;
             for (int o = threadIdx.x; o < ROWS * OCT_PER_ROW; o += NT) {
                 const int yl = o / OCT_PER_ROW, y = y0 + yl;
                 const int cx = (o % OCT_PER_ROW) * 8;
-                const int xa = (W >= 8) ? (x0 + cx) : (x0 & ~7);
+                const int xa = x0 + cx;
                 const uint64_t pix = (uint64_t)y * N + xa;
                 uint32_t u[8];
                 philox_block_u32(seed, r, pix >> 3, u);
@@ -186,10 +183,8 @@ k_ks_cols_fwd(const T* __restrict__ g1, const T* __restrict__ g2, long long g_st
                 load16<T, 8>(a2 + (long long)y * N + xa, gq);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    const int x = xa + i;
-                    if (W < 8 && (x < x0 || x >= x0 + W)) continue;
                     rotate_by_u32(u[i], gp[i], gq[i]);
-                    buf[yl * W + (x - x0)] = make_cpx(gp[i], gq[i]);
+                    buf[yl * W + cx + i] = make_cpx(gp[i], gq[i]);
                 }
             }
         } else {
@@ -335,19 +330,9 @@ struct RowHalf {
 // d) and a high lane (its partner's s, its s) in (d, s).
 template <int H>
 __device__ __forceinline__ void half_swap_u32(uint32_t& d, uint32_t& s, bool hi) {
-    if constexpr (H == 32) {
-        const auto r = __builtin_amdgcn_permlane32_swap(d, s, false, false);
-        d = r[0];
-        s = r[1];
-    } else if constexpr (H == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(d, s, false, false);
-        d = r[0];
-        s = r[1];
-    } else {
-        const uint32_t got = (uint32_t)__shfl_xor((int)(hi ? d : s), H);
-        if (hi) d = got;
-        else s = got;
-    }
+    const uint32_t got = (uint32_t)__shfl_xor((int)(hi ? d : s), H);
+    if (hi) d = got;
+    else s = got;
 }
 template <int H, typename T>
 __device__ __forceinline__ void half_swap(T& d, T& s, bool hi) {
@@ -448,7 +433,7 @@ __global__ void __launch_bounds__((RowHalf<T, LOGN>::NT))
 k_ks_rows_half(cpx<T>* __restrict__ C, const cpx<T>* __restrict__ tw, int nx) {
     using F = FS<LOGN>;
     using RP = RowHalf<T, LOGN>;
-    constexpr int N = F::N, N1 = F::N1, N2 = F::N2, RR = F::RR, EX = Row4<T, LOGN>::EX;
+    constexpr int N = F::N, N1 = F::N1, N2 = F::N2, RR = F::RR, EX = row4_elems<LOGN>();
     constexpr int M2 = N2 / 2, M1 = N1 / 2;  // values per lane in the two inverse steps
     // a unit (2 N2 lanes, aligned) lies in one wavefront, so wave-level
     // ordering covers its exchanges and its cross-lane steps
@@ -609,6 +594,13 @@ static int strip_width(int n, int cols, long long maps, int wmax, bool rotate) {
     return w;
 }
 
+// Which forward passes of a size run in four steps at all (ks_fwd): rotating
+// ones but for 4096 points, others but for 2048.
+template <int LOGN>
+constexpr bool fwd4_rotates() { return LOGN < 12; }
+template <int LOGN>
+constexpr bool fwd4_plain() { return LOGN != 11; }
+
 template <typename T, int LOGN, bool CROP, int WREQ>
 static hipError_t cols_fwd_w(const KsArgs<T>& a) {
     constexpr int N = 1 << LOGN;
@@ -621,15 +613,23 @@ static hipError_t cols_fwd_w(const KsArgs<T>& a) {
     // measured 4 to 6% slower at 1024^2 and 2048^2)
     const bool shared_in = a.g_stride == 0 && !a.g1_off && a.batch > 1;
     const int xcd = (!shared_in && S::W * (int)sizeof(T) < 128) ? 1 : 0;
-    if (a.rotate)
-        AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
-                    k_ks_cols_fwd<T, LOGN, true, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
-    else
-        AMAP_LAUNCH("ks_cols_fwd", a.stream,
-                    k_ks_cols_fwd<T, LOGN, false, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
-                        a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
-    return hipGetLastError();
+    if constexpr (fwd4_rotates<LOGN>() && WREQ >= 8) {
+        if (a.rotate) {
+            AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
+                        k_ks_cols_fwd<T, LOGN, true, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
+                            a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
+            return hipGetLastError();
+        }
+    }
+    if constexpr (fwd4_plain<LOGN>()) {
+        if (!a.rotate) {
+            AMAP_LAUNCH("ks_cols_fwd", a.stream,
+                        k_ks_cols_fwd<T, LOGN, false, CROP, WREQ><<<g, S::NT, 0, a.stream>>>(
+                            a.g1, a.g2, a.g_stride, a.g1_off, a.g2_off, a.C, a.seed, a.r0, a.tw, xcd, ny, nx));
+            return hipGetLastError();
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename T, int LOGN, bool CROP, int WREQ>
@@ -679,10 +679,10 @@ static hipError_t ks_fwd(const KsArgs<T>& a) {
     if constexpr (fwd3_always<T, LOGN, CROP>()) {
         return launch_ks3_fwd<T, LOGN, CROP>(a);
     } else {
-        if constexpr (LOGN == 12) {
+        if constexpr (!fwd4_rotates<LOGN>()) {
             if (a.rotate) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
-        if constexpr (LOGN == 11) {
+        if constexpr (!fwd4_plain<LOGN>()) {
             if (!a.rotate) return launch_ks3_fwd<T, LOGN, CROP>(a);
         }
         constexpr int N = 1 << LOGN, WF = StripF<T, LOGN>::W;

@@ -160,10 +160,6 @@ k_noise_finalize_parts(const A* __restrict__ part, NoiseParts np, int R, int B, 
     }
 }
 
-__global__ void k_zero_f64(double* p, long long count) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < count) p[i] = 0.0;
-}
 __global__ void k_zero_i64(long long* p, long long count) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i < count) p[i] = 0;
@@ -467,10 +463,6 @@ hipError_t launch_noise_finalize_parts(int logn, int J, int R, int B, const Nois
     return hipGetLastError();
 }
 
-hipError_t launch_zero_f64(double* p, long long count, hipStream_t s) {
-    if (count > 0) AMAP_LAUNCH("zero", s, k_zero_f64<<<blocks_for(count), 256, 0, s>>>(p, count));
-    return hipGetLastError();
-}
 hipError_t launch_zero_i64(long long* p, long long count, hipStream_t s) {
     if (count > 0) AMAP_LAUNCH("zero", s, k_zero_i64<<<blocks_for(count), 256, 0, s>>>(p, count));
     return hipGetLastError();
