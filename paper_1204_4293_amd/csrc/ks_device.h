@@ -85,9 +85,10 @@ __device__ __forceinline__ void strip_of(int xcd, int& s, int& b) {
     b = blockIdx.y;
     const int nx = gridDim.x;
     const int total = nx * gridDim.y;
-    if (xcd && (total & 7) == 0) {
-        const int l = blockIdx.x + nx * blockIdx.y;
-        const int v = (l & 7) * (total >> 3) + (l >> 3);
+    if (xcd) {
+        // XCD k runs workgroups k, k + 8, ..: one more where total is no multiple of 8
+        const int l = blockIdx.x + nx * blockIdx.y, k = l & 7;
+        const int v = k * (total >> 3) + min(k, total & 7) + (l >> 3);
         if (xcd == 2) {
             b = v % (int)gridDim.y;
             s = v / (int)gridDim.y;
