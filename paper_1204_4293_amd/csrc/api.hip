@@ -334,9 +334,9 @@ amap_status enqueue_starlet(const amap_ctx* ctx, int logn, int J, int batch, con
 // Realisations per launch sequence of the noise loop.
 int noise_batch(int n, int n_real) {
     const long long n2 = (long long)n * n;
-    // ~128 M pixels of realisations in flight: fewer merges of the float64
-    // running statistics (each reads and writes them once) and fewer launch
-    // tails; 4.5 GiB of workspace at 1024^2
+    // ~128 M pixels of realisations in flight: fewer partial statistics (each
+    // batch stores its own, the finalize kernel reads them all) and fewer
+    // launch tails; 4.5 GiB of workspace at 1024^2
     long long b = (1ll << 27) / n2;
     if (b < 1) b = 1;
     if (b > n_real) b = n_real;

@@ -47,7 +47,7 @@ k_noise_finalize(const double* __restrict__ M2, int R, int J, int logn, StatLayo
 // wavefront reads runs and not a line per lane; sigma goes through LDS (a
 // row padded by one per d pixels, against bank conflicts) into row order for
 // the stores.  The merge weights are worked out once per block.  Bound by its
-// reads (8 bytes a partial): 4096^2, J = 9, four batches, 1.3 ms; one lane
+// reads (8 bytes a partial): 4096^2, J = 9, four batches, 1.2 ms; one lane
 // per pixel in row order took 3.2.
 template <typename T, typename A>
 __global__ void __launch_bounds__(256)
