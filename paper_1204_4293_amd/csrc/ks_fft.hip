@@ -662,8 +662,8 @@ static hipError_t cols_inv_w(const KsArgs<T>& a) {
 //                  4096^2 x 8: 672 / 360
 //   forward pass:  rotating, 1024^2 x 128: 315 / 400; 2048^2 x 32: 430 / 488;
 //                  4096^2 x 8: 998 / 816
-//                  2048^2, one map: 41 / 21, two: 46 / 43, four: 83 / 86, eight:
-//                  187 / 190; one of 4096^2: 112 / 129
+//                  2048^2, one map: 41 / 21, two: 46 / 38, four: 68 / 80, eight:
+//                  154 / 158, twenty-five: 397 / 448; one of 4096^2: 112 / 129
 //                  rotating, 1000 x 1000 in 2048^2 x 15: 154 / 131
 // Double precision from 1024 points (whose per-thread DFTs would not fit the
 // registers) has three-step kernels only.

@@ -578,7 +578,7 @@ static hipError_t fwd3(const KsArgs<T>& a) {
     // realisations of one input: all of a strip's on one XCD (4096^2 float, 8
     // realisations: 816 us, 1129 strip by strip)
     const bool shared_in = a.g_stride == 0 && !a.g1_off && a.batch > 1;
-    const int xcd = shared_in ? 2 : W <= 8 ? 1 : 0;
+    const int xcd = shared_in ? 2 : 1;
     if constexpr (!fwd3_plain<T, LOGN, CROP>()) {
         if (a.rotate) {
             AMAP_LAUNCH("ks_cols_fwd_rotate", a.stream,
@@ -614,7 +614,8 @@ static hipError_t inv3(const KsArgs<T>& a) {
 // single precision, one where the launch is small (2048^2, one map: 20.4
 // against 22.1).  Maps of 2048^2 floats take sixteen columns, four items per
 // thread, from one workgroup per CU on (us, 8 / 16 columns: one map 21 / 30,
-// two 60 / 43, three 81 / 78, four 110 / 86, eight 217 / 190).  None of this
+// two 40 / 38, four 104 / 80, eight 194 / 158, twenty-five 504 / 448; not grouped
+// by XCD, where two strips share a line of the input, 514).  None of this
 // changes a map's values: strips and items only spread the same transforms.
 template <typename T, int LOGN, bool CROP>
 hipError_t launch_ks3_fwd(const KsArgs<T>& a) {
